@@ -567,11 +567,13 @@ int32_t enqueue_front(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& g, 
     ca.need_mask = (1u << NL) - 1u;
     ca.n_preds = L.n_preds;
     ca.pred_class_shift = L.pred_shift;
+    // < <= > >= == != as the outcomes below (1), equal (2), above (4)
+    static const uint32_t kWhen[6] = {1, 3, 4, 6, 2, 5};
     for (uint32_t q = 0; q < L.n_preds && q < 3; ++q) {
         ca.pred_dw[q] = L.pred[q].offset / 4;
         ca.pred_shift[q] = (L.pred[q].offset % 4) * 8;
         ca.pred_mask[q] = L.pred[q].bytes == 4 ? 0xFFFFFFFFu : ((1u << (8 * L.pred[q].bytes)) - 1u);
-        ca.pred_op[q] = L.pred[q].op;
+        ca.pred_when[q] = kWhen[L.pred[q].op];
         ca.pred_val[q] = L.pred[q].value;
     }
     ca.check_type_range = L.type_bytes > 1;
