@@ -94,6 +94,10 @@ struct ClassifyArgs {
     const uint32_t* rank[kMaxLevels];
 };
 
+// Tiles of a radix pass whose counts are summed as one: a tile's look-back
+// reads the tiles of its own group before it, and whole groups beyond.
+constexpr uint32_t kSortGroup = 16;
+
 struct SortPassArgs {
     const uint64_t* in;
     uint64_t* out;
@@ -101,7 +105,7 @@ struct SortPassArgs {
     uint32_t shift;                  // lowest bit of this pass's digit
     uint32_t nbits;                  // digit width (<= the kernel's digit bits)
     const uint32_t* hist;            // this pass's global histogram [buckets]
-    uint32_t* status;                // [tiles][buckets] look-back words
+    uint32_t* status;                // [tiles, then groups of tiles][buckets] look-back words
     uint32_t* ticket;
     const uint32_t* n_valid;         // non-null: words kept by the first pass (device)
     uint32_t drop_excl;              // first pass: words with bit excl_shift set are dropped
@@ -360,10 +364,16 @@ struct KeyValuesArgs {
 hipError_t launch_zero(const ZeroArgs& a, uint32_t blocks, hipStream_t s);
 hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s);
 hipError_t launch_sort_pass(const SortPassArgs& a, int variant, uint32_t digit_bits, hipStream_t s);
-uint32_t sort_threads(int variant);   // threads per block of a sort variant
-uint32_t sort_tile(int variant);      // words per radix tile of a sort variant
+// Block and words per thread of a sort variant for n words, and its look-back.
+struct SortShape {
+    uint32_t threads, items;
+    bool grouped;
+};
+SortShape sort_shape(int variant, uint64_t n);
+uint32_t sort_threads(int variant);
+uint64_t sort_status_rows(int variant, uint64_t n);   // look-back rows of a pass over up to n words
 constexpr int kSortVariants = 7;
-constexpr int kDefaultSortVariant = 1;     // 512 threads x 16 words
+constexpr int kDefaultSortVariant = 6;     // 1024 threads x 2..16 words, fitted to the trace
 hipError_t launch_scan(const ScanArgs& a, int variant, hipStream_t s);
 hipError_t launch_mapscan(const ScanArgs& a, int items, hipStream_t s);   // reduce, spine, down sweep
 uint32_t scan_tile(int variant);      // words per scan tile of a scan variant

@@ -20,6 +20,8 @@
 //                its children's verdicts (Def. 7 at every child node); at the
 //                root the last block also runs Def. 7 at the root.
 //   k_finalize   Def. 7 at the root of a one-level tree.
+#include <algorithm>
+
 #include "internal.h"
 #include "maps.h"
 
@@ -358,13 +360,26 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
 // ---------------------------------------------------------------------------
 constexpr uint32_t kFlagAgg = 1u << 30, kFlagInc = 2u << 30, kValMask = (1u << 30) - 1;
 constexpr int kSortLookWindow = 4;
-constexpr bool kSortSpinSleep = true;    // back off while a predecessor has not published
 
 // 16-item tiles are held to 128 VGPRs (two 512-thread blocks per CU), 8-item
 // tiles to 80 (three).  Tiles above 8192 words are written out in PHASES
 // parts through an LDS buffer of CHUNK words.  RB is the digit width of the
 // kernel (8: 256 buckets, 9: 512); one thread owns each bucket.
-template <int THREADS, int ITEMS, int RB>
+//
+// The words of a bucket in the tiles before this one come from look-back over
+// the tiles' published counts.  GROUPED: over the tiles of the own group of
+// kSortGroup (all in flight at once) and then whole groups, whose sums their
+// last tiles publish.  When all tiles start together, as in a launch of few
+// rounds, the plain chain walks half the launch's tiles four at a time before
+// it meets a total; over many rounds the tiles have drifted apart, a total is
+// close by and the plain chain reads less.  All passes of one sort, plain and
+// grouped: 100k words 31.3 and 27.9 us, 1M 70.6 and 63.1, 4M 111 and 102, 10M
+// 236 and 228, but 30M 697 and 733.
+//
+// What bounds a tile of 1024 x 16 words and 9-bit digits (17.9 us): loads 2.6,
+// ranking 7.0 (vector instructions: 65 per item and wave), scans and placing
+// 2.4, look-back 3.3, writes 2.7; one such block fills a CU's registers.
+template <int THREADS, int ITEMS, int RB, bool GROUPED>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(ITEMS <= 8 ? 6 : ITEMS <= 12 ? 5 : ITEMS <= 16 ? 4 : 2)))
 void k_sort_pass(SortPassArgs a) {
     constexpr int B = 1 << RB;
@@ -384,7 +399,7 @@ void k_sort_pass(SortPassArgs a) {
     __shared__ uint64_t s_buf[kShare ? (CHUNK > CNT64 ? CHUNK : CNT64) : CHUNK + CNT64];
     uint64_t* s_keys = s_buf;
     uint32_t* s_wcnt = reinterpret_cast<uint32_t*>(s_buf + (kShare ? 0 : CHUNK));   // [WAVES][B]
-    __shared__ uint32_t s_gbase[B];
+    __shared__ uint32_t s_gbase[B], s_tot[GROUPED ? B : 1], s_mine[GROUPED ? B : 1];
     __shared__ uint32_t s_tmp[2 * NB];
     __shared__ uint32_t s_tile;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -452,7 +467,8 @@ void k_sort_pass(SortPassArgs a) {
     if (tid < B) {
 #pragma unroll
         for (int ww = 0; ww < WAVES; ++ww) tot += s_wcnt[ww * B + tid];
-        st_flag(a.status + (uint64_t)tile * B + tid, (tile == 0 ? kFlagInc : kFlagAgg) | tot);
+        st_flag(a.status + (uint64_t)tile * B + tid, (!GROUPED && tile == 0 ? kFlagInc : kFlagAgg) | tot);
+        if (GROUPED) s_tot[tid] = tot;
     }
     const uint2 ex = block_excl_scan2<NB>(tot, h, s_tmp);
     const uint32_t lstart = ex.x, gexcl = ex.y;
@@ -484,41 +500,74 @@ void k_sort_pass(SortPassArgs a) {
         for (int r = 0; r < ITEMS; ++r)
             if (((vm >> r) & 1u) && (dr[r] >> RB) < (uint32_t)CHUNK) s_keys[dr[r] >> RB] = key[r];
     }
-    if (tid < B) {
-        uint32_t prefix = 0;
-        if (tile > 0) {
-            // windowed look-back: one round trip fetches kSortLookWindow
-            // predecessors of this bucket (consecutive buckets: coalesced)
-            int64_t j = (int64_t)tile - 1;
-            uint32_t spins = 0;
-            bool done = false;
-            while (!done) {
-                uint32_t sv[kSortLookWindow];
+    // words of every bucket in the tiles before this one: GROUPED, those of its
+    // own group (`mine`) and of the groups before (`before`), the two sums side
+    // by side when there are two threads per bucket
+    constexpr bool kTwo = GROUPED && THREADS >= 2 * B;
+    const uint32_t grp = tile / kSortGroup, l = tile % kSortGroup;
+    const uint32_t b = kTwo ? (uint32_t)tid % B : (uint32_t)tid;
+    uint32_t* chain = GROUPED ? a.status + (uint64_t)((a.n + TILE - 1) / TILE) * B : a.status;   // [groups or tiles][B]
+    if (GROUPED && (kTwo ? tid >= B && tid < 2 * B : tid < B)) {
+        uint32_t mine = 0, spins = 0;
+        const uint32_t* row = a.status + (uint64_t)grp * kSortGroup * B + b;
+        while (l > 0) {
+            uint32_t sv[kSortGroup - 1], all = kFlagAgg;
 #pragma unroll
-                for (int k = 0; k < kSortLookWindow; ++k)
-                    sv[k] = j - k >= 0 ? ld_acquire_flag(a.status + (uint64_t)(j - k) * B + tid) : kFlagInc;
-                int used = 0;
-                bool stop = false;
+            for (uint32_t k = 0; k < kSortGroup - 1; ++k)
+                sv[k] = k < l ? ld_acquire_flag(row + (uint64_t)k * B) : kFlagAgg;
+            mine = 0;
 #pragma unroll
-                for (int k = 0; k < kSortLookWindow; ++k) {
-                    if (done || stop) continue;
-                    if ((sv[k] >> 30) == 0u) { stop = true; continue; }   // not published yet: poll again from here
-                    prefix += sv[k] & kValMask;
-                    used = k + 1;
-                    if ((sv[k] & ~kValMask) == kFlagInc) done = true;
-                }
-                j -= used;
-                if (!done && j < 0) done = true;
-                if (!done && used == 0) {
-                    if (++spins > kSpinLimit) {
-                        atomicOr(a.err, kErrSpin);
-                        break;
-                    }
-                    if (kSortSpinSleep) __builtin_amdgcn_s_sleep(1);
-                }
+            for (uint32_t k = 0; k < kSortGroup - 1; ++k) {
+                all &= sv[k];
+                mine += sv[k] & kValMask;
             }
-            st_flag(a.status + (uint64_t)tile * B + tid, kFlagInc | (prefix + tot));
+            if (all & kFlagAgg) break;
+            if (++spins > kSpinLimit) {
+                atomicOr(a.err, kErrSpin);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
         }
+        if (l == kSortGroup - 1) st_flag(chain + (uint64_t)grp * B + b, (grp == 0 ? kFlagInc : kFlagAgg) | (mine + s_tot[b]));
+        s_mine[b] = mine;
+    }
+    uint32_t before = 0;
+    if (tid < B) {
+        // windowed look-back: one round trip fetches kSortLookWindow
+        // predecessors of this bucket (consecutive buckets: coalesced)
+        int64_t j = (int64_t)(GROUPED ? grp : tile) - 1;
+        uint32_t spins = 0;
+        bool done = j < 0;
+        while (!done) {
+            uint32_t sv[kSortLookWindow];
+#pragma unroll
+            for (int k = 0; k < kSortLookWindow; ++k)
+                sv[k] = j - k >= 0 ? ld_acquire_flag(chain + (uint64_t)(j - k) * B + b) : kFlagInc;
+            int used = 0;
+            bool stop = false;
+#pragma unroll
+            for (int k = 0; k < kSortLookWindow; ++k) {
+                if (done || stop) continue;
+                if ((sv[k] >> 30) == 0u) { stop = true; continue; }   // not published yet: poll again from here
+                before += sv[k] & kValMask;
+                used = k + 1;
+                if ((sv[k] & ~kValMask) == kFlagInc) done = true;
+            }
+            j -= used;
+            if (!done && used == 0) {
+                if (++spins > kSpinLimit) {
+                    atomicOr(a.err, kErrSpin);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+    }
+    if (kTwo) __syncthreads();
+    if (tid < B) {
+        const uint32_t prefix = before + (GROUPED ? s_mine[tid] : 0u);
+        if (GROUPED ? l == kSortGroup - 1 && grp > 0 : tile > 0)
+            st_flag(chain + (uint64_t)(GROUPED ? grp : tile) * B + tid, kFlagInc | (prefix + tot));
         s_gbase[tid] = gexcl + prefix - lstart;     // destination of tile position i of bucket d: s_gbase[d] + i
     }
     __syncthreads();
@@ -1694,42 +1743,93 @@ hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-uint32_t sort_tile(int variant) {
+// Variant 6 fits its tile to the trace: blocks of 1,024 threads, one to a CU,
+// so tiles run in rounds of kCus and the last round may be nearly empty.  A
+// tile of `items` words a thread takes about 4.5 + 0.83 items us (measured at
+// 16 items; 4.5 is the scans and the look-back, whatever the items); the items
+// that make the fewest such microseconds over all rounds win.  All passes of a
+// sort: 100k words 2 items 27.9 us (16: 51.1), 1M 4 items 63.1 (16: 80.5), 2M 8
+// items 76 (16: 90), 6M 12 items 156 (16: 169), 10M 13 items 228 (16: 242).
+// Beyond four rounds of 16 items the rounds hardly matter (30M: 13 items 3 %
+// slower), and the plain look-back chain is the faster one.
+constexpr uint32_t kCus = 256;
+SortShape sort_shape(int variant, uint64_t n) {
     switch (variant) {
-        case 1: return 512 * 16;
-        case 2: return 256 * 24;
-        case 3: return 256 * 8;
-        case 4: return 512 * 8;
-        case 5: return 512 * 12;
-        case 6: return 1024 * 16;
-        default: return 256 * 16;
+        case 0: return {256, 16, false};
+        case 1: return {512, 16, false};
+        case 2: return {256, 24, false};
+        case 3: return {256, 8, false};
+        case 4: return {512, 8, false};
+        case 5: return {512, 12, false};
+        default: break;
     }
+    SortShape best{1024, 16, false};
+    if (n > 4ull * kCus * 1024 * 16) return best;
+    uint64_t least = ~0ull;
+    for (uint32_t items : {2u, 4u, 6u, 8u, 10u, 12u, 13u, 14u, 16u}) {
+        const uint64_t tiles = (n + 1024 * items - 1) / (1024 * items), rounds = (tiles + kCus - 1) / kCus;
+        const uint64_t cost = rounds * (450 + 83 * items);
+        if (cost < least) {
+            least = cost;
+            best = {1024, items, true};
+        }
+    }
+    return best;
 }
 
-uint32_t sort_threads(int variant) { return variant == 6 ? 1024u : variant == 1 || variant == 4 || variant == 5 ? 512u : 256u; }
+// Tiles, plus groups of them.  At least those of any smaller n, so that a
+// workspace planned for n serves every smaller call too: variant 6 never takes
+// more rounds for fewer words, but may take more tiles in as many rounds.
+uint64_t sort_status_rows(int variant, uint64_t n) {
+    const SortShape sh = sort_shape(variant, n);
+    uint64_t tiles = (n + sh.threads * sh.items - 1) / (sh.threads * sh.items);
+    if (variant >= 6 || variant < 0) {
+        tiles = sh.grouped ? std::min<uint64_t>((n + 2047) / 2048, (tiles + kCus - 1) / kCus * kCus)
+                           : std::max<uint64_t>(4 * kCus, tiles);
+        tiles += (tiles + kSortGroup - 1) / kSortGroup;
+    }
+    return tiles;
+}
+
+uint32_t sort_threads(int variant) { return sort_shape(variant, 0).threads; }
+
+template <int T, int I, bool G>
+static void launch_sort_t(const SortPassArgs& a, uint32_t digit_bits, hipStream_t s) {
+    const dim3 grid((a.n + T * I - 1) / (T * I)), block(T);
+    if constexpr (T >= 512) {
+        if (digit_bits == 9) {
+            hipLaunchKernelGGL((k_sort_pass<T, I, 9, G>), grid, block, 0, s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_sort_pass<T, I, 8, G>), grid, block, 0, s, a);
+}
 
 hipError_t launch_sort_pass(const SortPassArgs& a, int variant, uint32_t digit_bits, hipStream_t s) {
-    const uint32_t tile = sort_tile(variant);
-    const uint32_t tiles = (a.n + tile - 1) / tile;
-    if (digit_bits == 9) {
-        switch (variant) {
-            case 1: hipLaunchKernelGGL((k_sort_pass<512, 16, 9>), dim3(tiles), dim3(512), 0, s, a); break;
-            case 4: hipLaunchKernelGGL((k_sort_pass<512, 8, 9>), dim3(tiles), dim3(512), 0, s, a); break;
-            case 5: hipLaunchKernelGGL((k_sort_pass<512, 12, 9>), dim3(tiles), dim3(512), 0, s, a); break;
-            case 6: hipLaunchKernelGGL((k_sort_pass<1024, 16, 9>), dim3(tiles), dim3(1024), 0, s, a); break;
-            default: return hipErrorInvalidValue;
+    const SortShape sh = sort_shape(variant, a.n);
+    if (digit_bits != 8 && !(digit_bits == 9 && sh.threads >= 512)) return hipErrorInvalidValue;
+    if (sh.threads == 256) {
+        if (sh.items == 8) launch_sort_t<256, 8, false>(a, digit_bits, s);
+        else if (sh.items == 24) launch_sort_t<256, 24, false>(a, digit_bits, s);
+        else launch_sort_t<256, 16, false>(a, digit_bits, s);
+    } else if (sh.threads == 512) {
+        if (sh.items == 8) launch_sort_t<512, 8, false>(a, digit_bits, s);
+        else if (sh.items == 12) launch_sort_t<512, 12, false>(a, digit_bits, s);
+        else launch_sort_t<512, 16, false>(a, digit_bits, s);
+    } else if (!sh.grouped) {
+        launch_sort_t<1024, 16, false>(a, digit_bits, s);
+    } else {
+        switch (sh.items) {
+            case 2: launch_sort_t<1024, 2, true>(a, digit_bits, s); break;
+            case 4: launch_sort_t<1024, 4, true>(a, digit_bits, s); break;
+            case 6: launch_sort_t<1024, 6, true>(a, digit_bits, s); break;
+            case 8: launch_sort_t<1024, 8, true>(a, digit_bits, s); break;
+            case 10: launch_sort_t<1024, 10, true>(a, digit_bits, s); break;
+            case 12: launch_sort_t<1024, 12, true>(a, digit_bits, s); break;
+            case 13: launch_sort_t<1024, 13, true>(a, digit_bits, s); break;
+            case 14: launch_sort_t<1024, 14, true>(a, digit_bits, s); break;
+            default: launch_sort_t<1024, 16, true>(a, digit_bits, s); break;
         }
-        return hipGetLastError();
-    }
-    if (digit_bits != 8) return hipErrorInvalidValue;
-    switch (variant) {
-        case 1: hipLaunchKernelGGL((k_sort_pass<512, 16, 8>), dim3(tiles), dim3(512), 0, s, a); break;
-        case 2: hipLaunchKernelGGL((k_sort_pass<256, 24, 8>), dim3(tiles), dim3(256), 0, s, a); break;
-        case 3: hipLaunchKernelGGL((k_sort_pass<256, 8, 8>), dim3(tiles), dim3(256), 0, s, a); break;
-        case 4: hipLaunchKernelGGL((k_sort_pass<512, 8, 8>), dim3(tiles), dim3(512), 0, s, a); break;
-        case 5: hipLaunchKernelGGL((k_sort_pass<512, 12, 8>), dim3(tiles), dim3(512), 0, s, a); break;
-        case 6: hipLaunchKernelGGL((k_sort_pass<1024, 16, 8>), dim3(tiles), dim3(1024), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_sort_pass<256, 16, 8>), dim3(tiles), dim3(256), 0, s, a); break;
     }
     return hipGetLastError();
 }

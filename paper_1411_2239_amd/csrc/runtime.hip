@@ -196,7 +196,8 @@ struct WsLayout {
     uint64_t words_a_off, words_b_off, inst_verdict_off, inst_parent_off, inst_start_off;
     uint64_t node_start_off[kMaxLevels], counts_off[kMaxLevels];
     uint64_t cap_node[kMaxLevels];
-    uint32_t tiles_sort, tiles_scan;
+    uint64_t sort_rows;                    // look-back rows of a radix pass
+    uint32_t tiles_scan;
     uint64_t ms_desc_off, ms_agg_off, ms_prefix_off, ms_trec_off, ms_chunk_off;   // the split map scan
     uint32_t ms_tiles;
     // parent events
@@ -257,8 +258,7 @@ std::vector<uint32_t> monitor_states(const ltl4c_ctx* ctx, const int32_t* props,
 WsLayout plan_workspace(const ltl4c_layout& L, const Geometry& g, uint64_t n, uint32_t P, uint32_t n_scan_groups,
                         int sort_variant, int scan_variant) {
     WsLayout w{};
-    const uint64_t st = sort_tile(sort_variant);
-    w.tiles_sort = (uint32_t)((n + st - 1) / st);
+    w.sort_rows = sort_status_rows(sort_variant, n);
     const uint64_t sct = scan_tile(scan_variant);
     w.tiles_scan = (uint32_t)((n + sct - 1) / sct);
     // zero block, in 32-bit words
@@ -270,7 +270,7 @@ WsLayout plan_workspace(const ltl4c_layout& L, const Geometry& g, uint64_t n, ui
     w.root_counts_off = z; z += kMaxProps * 6;
     w.sizes32_off = z;     z += 64;
     w.sizes64_off = z;     z += 64;                      // 32 x uint64
-    w.sort_status_off = z; z += ((uint64_t)g.n_pass * w.tiles_sort) << g.digit_bits;
+    w.sort_status_off = z; z += (g.n_pass * w.sort_rows) << g.digit_bits;
     z = (z + 63) & ~63ull;
     w.scan_status_off = z; z += (uint64_t)n_scan_groups * w.tiles_scan * (2 * kScanRows);   // 2 kinds x 32-bit words
     z = (z + 63) & ~63ull;
@@ -385,18 +385,17 @@ struct RankRegion {
     uint64_t distinct_off;                // [4] distinct values per level
     uint64_t tile_cnt_off, tile_off_off;
     uint64_t rank_off[kMaxLevels], uniq_off[kMaxLevels];
-    uint32_t tiles_sort;
+    uint64_t sort_rows;
     uint64_t total;
 };
 
 RankRegion rank_region(const ltl4c_layout& L, uint64_t n, int sort_variant) {
     RankRegion r{};
-    const uint64_t st = sort_tile(sort_variant);
-    r.tiles_sort = (uint32_t)((n + st - 1) / st);
+    r.sort_rows = sort_status_rows(sort_variant, n);
     r.hist_w = 0;
     r.ticket_w = 4 * 256;
     r.status_w = r.ticket_w + 64;
-    r.zero_words = r.status_w + 4ull * r.tiles_sort * 256;
+    r.zero_words = r.status_w + 4ull * r.sort_rows * 256;
     uint64_t off = 0;
     r.zero_off = off;       off = align256(off + 4 * r.zero_words);
     r.distinct_off = off;   off = align256(off + 64);
@@ -610,7 +609,7 @@ int32_t enqueue_front(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& g, 
         sa.shift = g.cbits + g.ibits + g.digit_bits * p;
         sa.nbits = std::min<uint32_t>(g.digit_bits, g.sort_bits - g.digit_bits * p);
         sa.hist = hist + ((uint64_t)p << g.digit_bits);
-        sa.status = sort_status + (((uint64_t)p * w.tiles_sort) << g.digit_bits);
+        sa.status = sort_status + ((p * w.sort_rows) << g.digit_bits);
         sa.ticket = sort_ticket + p;
         sa.n_valid = ca.n_valid;
         sa.drop_excl = g.compact && p == 0 ? 1u : 0u;
@@ -1346,7 +1345,7 @@ static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* 
             sa.shift = 32 + 8 * p;
             sa.nbits = 8;
             sa.hist = z + rr.hist_w + 256 * p;
-            sa.status = z + rr.status_w + (uint64_t)p * rr.tiles_sort * 256;
+            sa.status = z + rr.status_w + p * rr.sort_rows * 256;
             sa.ticket = z + rr.ticket_w + p;
             sa.err = ctx->err_dev;
             s = launch(ctx, "rank", [&] { return launch_sort_pass(sa, ctx->sort_variant, 8, st); });
