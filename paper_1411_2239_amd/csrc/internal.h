@@ -138,6 +138,8 @@ struct ScanArgs {
     uint32_t* inst_start;                // with inst_conc: sorted position of every instance's first word
     uint8_t* event_verdict;              // optional [n_props_all][n_events]: verdict after every event, trace order
     uint64_t n_events;                   // row stride of event_verdict
+    uint32_t* event_pack;                // split map scan, with event_verdict: 4 bits per property of the
+                                         // launch, by trace index, [n_events + 8]; all ones: no instance
     uint32_t class_mask;                 // class bits of a word (below the trace index, if any)
     uint32_t index_shift, index_mask;    // trace index of a word: (word >> index_shift) & index_mask
     uint64_t* node_keys[kMaxLevels];     // optional
@@ -376,6 +378,7 @@ constexpr int kSortVariants = 7;
 constexpr int kDefaultSortVariant = 6;     // 1024 threads x 2..16 words, fitted to the trace
 hipError_t launch_scan(const ScanArgs& a, int variant, hipStream_t s);
 hipError_t launch_mapscan(const ScanArgs& a, int items, hipStream_t s);   // reduce, spine, down sweep
+hipError_t launch_event_unpack(const ScanArgs& a, hipStream_t s);   // event_pack -> event_verdict
 uint32_t scan_tile(int variant);      // words per scan tile of a scan variant
 constexpr int kScanVariants = 6;
 constexpr int kSplitScanVariant = 4;       // reduce / spine / down sweep (mapscan.hip), 16 words a thread

@@ -1138,12 +1138,20 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
             sa.inst_conc = out->inst_conclusive;
             sa.inst_start = inst_start;
         }
+        const bool split = ctx->scan_variant == kSplitScanVariant || ctx->scan_variant == kSplitScanVariant32;
+        uint8_t* pack = nullptr;
         if (out->event_verdict) {
-            // events that join no cluster keep "no instance"
-            s = launch(ctx, "fill", [&] { return launch_fill_u8(out->event_verdict, LTL4C_NO_INSTANCE, (uint64_t)P * n, st); });
-            if (s) return s;
             sa.event_verdict = out->event_verdict;
             sa.n_events = n;
+            if (split) {
+                // packed in the word buffer the sort left, one launch's properties at a time
+                pack = ws + (sorted == words_a ? w.words_b_off : w.words_a_off);
+                sa.event_pack = reinterpret_cast<uint32_t*>(pack);
+            } else {
+                // events that join no cluster keep "no instance"
+                s = launch(ctx, "fill", [&] { return launch_fill_u8(out->event_verdict, LTL4C_NO_INSTANCE, (uint64_t)P * n, st); });
+                if (s) return s;
+            }
         }
         sa.sizes = sizes64;
         sa.sizes32 = sizes32;
@@ -1153,7 +1161,6 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
         // The split map scan (reduce, spine, down sweep; its down sweep also
         // writes the verdict timeline on request).  With parent events it
         // numbers the own events (the verdicts come after).
-        const bool split = ctx->scan_variant == kSplitScanVariant || ctx->scan_variant == kSplitScanVariant32;
         if (split) {
             if (!sa.n_dev) {
                 // nothing is excluded: every word counts
@@ -1179,8 +1186,14 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
             sa.ticket = scan_ticket + gi;
             if (split) {
                 sa.read_desc = gi > 0 ? 1u : 0u;    // the first launch wrote the descriptors
+                if (pack && g.excl) {
+                    // events that join no cluster keep "no instance"
+                    s = launch(ctx, "fill", [&] { return launch_fill_u8(pack, (uint8_t)0xFF, (sa.n_props <= 4 ? 2 : 4) * n, st); });
+                    if (s) return s;
+                }
                 const int items = ctx->scan_variant == kSplitScanVariant32 ? 32 : 16;
                 s = launch(ctx, "scan", [&] { return launch_mapscan(sa, items, st); });
+                if (s == LTL4C_OK && pack) s = launch(ctx, "timeline", [&] { return launch_event_unpack(sa, st); });
             } else {
                 s = launch(ctx, "scan", [&] { return launch_scan(sa, ctx->scan_variant, st); });
             }
