@@ -376,6 +376,7 @@ uint32_t sort_threads(int variant);
 uint64_t sort_status_rows(int variant, uint64_t n);   // look-back rows of a pass over up to n words
 constexpr int kSortVariants = 7;
 constexpr int kDefaultSortVariant = 6;     // 1024 threads x 2..16 words, fitted to the trace
+constexpr int kSmallSortVariant = 7;       // 1024 x 16 always: the fewest look-back rows (workspaces too small for 6)
 hipError_t launch_scan(const ScanArgs& a, int variant, hipStream_t s);
 hipError_t launch_mapscan(const ScanArgs& a, int items, hipStream_t s);   // reduce, spine, down sweep
 hipError_t launch_event_unpack(const ScanArgs& a, hipStream_t s);   // event_pack -> event_verdict

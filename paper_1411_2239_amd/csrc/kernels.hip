@@ -1764,7 +1764,7 @@ SortShape sort_shape(int variant, uint64_t n) {
         default: break;
     }
     SortShape best{1024, 16, false};
-    if (n > 4ull * kCus * 1024 * 16) return best;
+    if (variant == kSmallSortVariant || n > 4ull * kCus * 1024 * 16) return best;
     uint64_t least = ~0ull;
     for (uint32_t items : {2u, 4u, 6u, 8u, 10u, 12u, 13u, 14u, 16u}) {
         const uint64_t tiles = (n + 1024 * items - 1) / (1024 * items), rounds = (tiles + kCus - 1) / kCus;
@@ -1783,7 +1783,7 @@ SortShape sort_shape(int variant, uint64_t n) {
 uint64_t sort_status_rows(int variant, uint64_t n) {
     const SortShape sh = sort_shape(variant, n);
     uint64_t tiles = (n + sh.threads * sh.items - 1) / (sh.threads * sh.items);
-    if (variant >= 6 || variant < 0) {
+    if (variant == kDefaultSortVariant) {
         tiles = sh.grouped ? std::min<uint64_t>((n + 2047) / 2048, (tiles + kCus - 1) / kCus * kCus)
                            : std::max<uint64_t>(4 * kCus, tiles);
         tiles += (tiles + kSortGroup - 1) / kSortGroup;

@@ -1449,6 +1449,12 @@ static int32_t eval_impl(ltl4c_ctx* ctx, const void* d_records, uint64_t n, cons
         w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
         rbytes = ranked ? rank_region(L, n, ctx->sort_variant).total : 0;
     }
+    if (ws_bytes < rbytes + w.total && ctx->sort_variant == kDefaultSortVariant) {
+        // the largest tiles need the least look-back memory (the library's own scratch near its limit)
+        ctx->sort_variant = kSmallSortVariant;
+        w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
+        rbytes = ranked ? rank_region(L, n, ctx->sort_variant).total : 0;
+    }
     if (ws_bytes < rbytes + w.total) {
         if (!noalloc) return fail(LTL4C_ENOMEM, "workspace smaller than ltl4c_workspace_bytes()");
         char buf[200];
@@ -1641,6 +1647,11 @@ static int32_t batch_impl(ltl4c_ctx* ctx, const void* d_records, const uint64_t*
     if (s) return s;
     if (ws_bytes < b.total && sc.changed()) {
         sc.revert();
+        s = batch_layout(ctx, n, n_traces, P, (uint32_t)groups.size(), &b);
+        if (s) return s;
+    }
+    if (ws_bytes < b.total && ctx->sort_variant == kDefaultSortVariant) {
+        ctx->sort_variant = kSmallSortVariant;
         s = batch_layout(ctx, n, n_traces, P, (uint32_t)groups.size(), &b);
         if (s) return s;
     }

@@ -56,3 +56,26 @@ def test_workspace_serves_smaller_traces():
     need = [ctx.workspace_bytes(n, ids) for n in edges]
     assert need == sorted(need)
     ctx.close()
+
+
+def test_small_workspace_takes_the_largest_tiles():
+    import torch
+    wl = W.gen_user_requests(n_events=1_500_000, n_users=300, seed=8)
+    ctx = lib.Context(0, use_tuned=False)
+    ctx.set_layout(wl.layout)
+    ids = [ctx.add_spec(p) for p in wl.props]
+    rec = torch.from_numpy(np.ascontiguousarray(wl.raw())).to("cuda:0")
+    n = wl.n_events
+    full = ctx.workspace_bytes(n, ids)
+    ctx.set_option(lib.OPT_SORT_TILE, 1)
+    less = ctx.workspace_bytes(n, ids)
+    ctx.set_option(lib.OPT_SORT_TILE, -1)
+    assert less < full
+    ws = torch.empty(less, dtype=torch.uint8, device="cuda:0")
+    r = ctx.alloc_result(len(ids), n, instances=True)
+    ctx.eval_into(rec, n, ids, r, ws)
+    ctx.wait()
+    compare_full(r, evaluate_workload(wl), len(ids), 2, check_nodes=False)
+    with pytest.raises(lib.LTL4CError):
+        ctx.eval_into(rec, n, ids, r, ws[:less // 2])
+    ctx.close()
