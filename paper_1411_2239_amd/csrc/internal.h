@@ -87,7 +87,8 @@ struct ClassifyArgs {
     // parent events: a type whose key_present bits (within need_mask) equal
     // parent_mask carries every key but the innermost; such an event gets
     // the innermost key 0 and the kind bit at stream_shift, and is counted in
-    // n_par.  parent_mask > need_mask: no parent events.
+    // n_par[0] (the other kept events in n_par[1]).  parent_mask > need_mask:
+    // no parent events.
     uint32_t parent_mask;
     uint32_t* n_par;
     // ranked keys: key m of event i is rank[m][i] instead of its record field
@@ -293,39 +294,28 @@ struct BatchOutArgs {
 constexpr int kPeThreads = 256;
 constexpr int kPeItems = 16;
 constexpr int kPeTile = kPeThreads * kPeItems;
-constexpr int kPeSpineThreads = 1024;
 constexpr int kPeShortGap = 8;          // gaps up to this many parent entries skip the segment tree
-constexpr int kPeShortRun = 8;          // a parent's run up to this long is held in registers
-constexpr int kPeSamples = 2048;        // sample table of the parent array (fits the word rows in LDS)
-static_assert(kPeSamples <= kPeItems * kPeThreads, "samples share LDS with the staged words");
 constexpr int kPeTreeLevelsPerLaunch = 8;
 constexpr int kPeMaxTreeLevels = 33;
 struct ParentArgs {
     const uint64_t* words;
-    const uint32_t* n_kept;              // events kept by classify (own + parent)
-    uint32_t* n_par;                     // parent events (classify counts them)
-    uint32_t* n_own;                     // own events (k_pe_counts)
+    const uint32_t* n_par;               // parent events and own events kept (classify counts both)
+    const uint32_t* n_own;
     uint32_t cbits;                      // class bits
     uint32_t class_mask;
     uint32_t ibits;                      // trace index bits above the class
     uint64_t index_mask;
-    uint32_t key_shift;                  // word >> key_shift: the packed key (instance identity)
     uint32_t prefix_shift;               // (word >> prefix_shift) & prefix_mask: keys 0..n-2
     uint64_t prefix_mask;
     uint32_t n_props;
     const Plan* plan;
-    uint4* tree;                         // segment tree levels 1..: [level][p][tree_cnt[level]]
-    uint64_t tree_off[kPeMaxTreeLevels]; // in uint4 units
+    uint2* tree;                         // segment tree levels 1..: [level][p][tree_cnt[level]], 4-bit maps
+    uint64_t tree_off[kPeMaxTreeLevels]; // in nodes
     uint64_t tree_cnt[kPeMaxTreeLevels];
-    uint4* tile_agg;                     // [tiles][P]
-    uint4* tile_prefix;                  // [tiles][P]
-    uint4* trec;                         // [P][tiles * kPeThreads] each thread's run map
-    uint64_t* samples;                   // [kPeSamples] keys of every stride-th parent entry
-    uint32_t* tile_heads;                // [tiles]
-    uint32_t* tile_head_prefix;          // [tiles]
-    uint8_t* inst_verdict;               // [P][inst_stride]
-    uint64_t inst_stride, inst_limit;
-    uint32_t* err;
+    uint32_t* bound;                     // [n_own] entries before every own event, and two flags (parent.h)
+    uint64_t cap;                        // row stride of pre and suf
+    uint8_t* pre;                        // [p][cap] state from q0 through the run up to and with the entry
+    uint2* suf;                          // [p][cap] map of the run from the entry on, 4 bits per state
 };
 
 // Key ranking (composite keys wider than the sort word): per level, every
@@ -378,7 +368,8 @@ constexpr int kSortVariants = 7;
 constexpr int kDefaultSortVariant = 6;     // 1024 threads x 2..16 words, fitted to the trace
 constexpr int kSmallSortVariant = 7;       // 1024 x 16 always: the fewest look-back rows (workspaces too small for 6)
 hipError_t launch_scan(const ScanArgs& a, int variant, hipStream_t s);
-hipError_t launch_mapscan(const ScanArgs& a, int items, hipStream_t s);   // reduce, spine, down sweep
+// reduce, spine, down sweep; pe: merge parent events in (16 words a thread)
+hipError_t launch_mapscan(const ScanArgs& a, int items, const ParentArgs* pe, hipStream_t s);
 hipError_t launch_event_unpack(const ScanArgs& a, hipStream_t s);   // event_pack -> event_verdict
 uint32_t scan_tile(int variant);      // words per scan tile of a scan variant
 constexpr int kScanVariants = 6;
@@ -409,11 +400,9 @@ hipError_t launch_group_read(const GroupState& g, uint8_t* verdict, uint64_t* co
 hipError_t launch_fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_fill_u8(uint8_t* p, uint64_t n, uint8_t v, hipStream_t s);
 hipError_t launch_batch_out(const BatchOutArgs& a, hipStream_t s);
-hipError_t launch_parent_counts(const ParentArgs& a, hipStream_t s);
-hipError_t launch_parent_samples(const ParentArgs& a, hipStream_t s);
 hipError_t launch_parent_tree(const ParentArgs& a, uint32_t level0, uint32_t nlev, uint64_t max_nodes0, hipStream_t s);
-hipError_t launch_parent_pass(const ParentArgs& a, bool down, uint64_t max_tiles, hipStream_t s);
-hipError_t launch_parent_spine(const ParentArgs& a, hipStream_t s);
+hipError_t launch_parent_affix(const ParentArgs& a, uint64_t max_entries, hipStream_t s);
+hipError_t launch_parent_bounds(const ParentArgs& a, uint64_t max_own, hipStream_t s);
 hipError_t launch_rank_prep(const RankArgs& a, hipStream_t s);
 hipError_t launch_rank_scan(const RankArgs& a, hipStream_t s);
 hipError_t launch_key_values(const KeyValuesArgs& a, uint64_t max_n, hipStream_t s);

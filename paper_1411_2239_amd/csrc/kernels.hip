@@ -352,7 +352,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         if (v) atomicAdd(a.hist + i, v);
     }
     if (a.n_valid && threadIdx.x == 0 && s_nvalid) atomicAdd(a.n_valid, s_nvalid);
-    if (a.n_par && threadIdx.x == 64 && s_npar) atomicAdd(a.n_par, s_npar);
+    if (a.n_par && threadIdx.x == 64) {
+        if (s_npar) atomicAdd(a.n_par, s_npar);
+        if (s_nvalid > s_npar) atomicAdd(a.n_par + 1, s_nvalid - s_npar);
+    }
 }
 
 // ---------------------------------------------------------------------------

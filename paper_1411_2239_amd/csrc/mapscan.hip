@@ -18,14 +18,20 @@
 // (class, head and level-head flags); the down sweep and the launches of
 // further property groups read those instead of the words.  No tile waits on
 // another, so several tiles share a CU.
-#include "internal.h"
-#include "maps.h"
+#include <type_traits>
+
+#include "parent.h"
 
 namespace ltl4c {
 
 namespace {
 
 constexpr uint32_t kAll = 0xFFFFFFFFu;
+
+// PE kernels merge parent events in (parent.hip prepares what they read).
+struct NoParent {};
+template <bool PE>
+using PeParam = std::conditional_t<PE, ParentArgs, NoParent>;
 
 // Flags and classes of a thread's run of words: `cnt` valid words (a prefix of
 // the run), head (a new instance), level-m heads (a new level-m node), classes
@@ -154,17 +160,17 @@ __device__ __forceinline__ Run run_from_desc(const ScanArgs& a, uint64_t my0, ui
     return r;
 }
 
-// The composed map of a run per property: a head restarts the monitor at q0.
-// FULL: every word of the run is valid (all threads but the trace's last).
+// The composed map of a run per property: a head restarts the monitor at
+// `start` (only the last head's start shows in the result).  FULL: every word of the run is valid (all threads but the trace's last).
 template <int PMAX, int MW, int ITEMS, bool FULL>
 __device__ __forceinline__ void run_maps_t(const Run& r, uint32_t P, const uint32_t (*s_cm)[16][MW],
-                                           const uint32_t* s_q0, BMap<MW>* f) {
+                                           const uint32_t* start_q, BMap<MW>* f) {
     const uint32_t valid = FULL ? kAll : valid_mask(r.cnt);
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
         f[p] = bm_identity<MW>();
         if (p > 0 && p >= (int)P) continue;    // (a launch has at least one property)
-        const BMap<MW> start = bm_const<MW>(s_q0[p]);
+        const BMap<MW> start = bm_const<MW>(start_q[p]);
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
             const BMap<MW> cm = bm_load<MW>(s_cm[p][run_class(r, j)]);
@@ -174,11 +180,45 @@ __device__ __forceinline__ void run_maps_t(const Run& r, uint32_t P, const uint3
     }
 }
 template <int PMAX, int MW, int ITEMS>
-__device__ __forceinline__ void run_maps(const Run& r, uint32_t P, const uint32_t (*s_cm)[16][MW], const uint32_t* s_q0,
+__device__ __forceinline__ void run_maps(const Run& r, uint32_t P, const uint32_t (*s_cm)[16][MW], const uint32_t* start_q,
                                          BMap<MW>* f) {
     // (four 16-state maps keep the one path: the second copy costs them registers)
-    if (PMAX * MW <= 8 && r.cnt == ITEMS) run_maps_t<PMAX, MW, ITEMS, true>(r, P, s_cm, s_q0, f);
-    else run_maps_t<PMAX, MW, ITEMS, false>(r, P, s_cm, s_q0, f);
+    if (PMAX * MW <= 8 && r.cnt == ITEMS) run_maps_t<PMAX, MW, ITEMS, true>(r, P, s_cm, start_q, f);
+    else run_maps_t<PMAX, MW, ITEMS, false>(r, P, s_cm, start_q, f);
+}
+
+// The bounds of a run's own events, and the events whose gap to the event
+// before them (of the same instance) holds parent entries.
+struct Bounds {
+    uint32_t g[16];
+    uint32_t gaps;
+};
+__device__ __forceinline__ Bounds load_bounds(const ParentArgs& q, uint64_t my0, const Run& r) {
+    Bounds b;
+    const uint64_t at = r.cnt ? my0 : 0;         // unconditional loads; the array is followed by others
+    const uint4* src = reinterpret_cast<const uint4*>(q.bound + at);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint4 v = src[k];
+        b.g[4 * k] = v.x;
+        b.g[4 * k + 1] = v.y;
+        b.g[4 * k + 2] = v.z;
+        b.g[4 * k + 3] = v.w;
+    }
+    const uint32_t before = q.bound[at ? at - 1 : 0];
+    b.gaps = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+        b.gaps |= (uint32_t)((b.g[j] & kPeIndex) > ((j ? b.g[j - 1] : before) & kPeIndex)) << j;
+    b.gaps &= valid_mask(r.cnt) & ~r.m_head;
+    return b;
+}
+// property p's state before an instance's first own event with bound g (the
+// load is unconditional, so that those of a run are in flight together)
+__device__ __forceinline__ uint32_t pe_start(const ParentArgs& q, uint32_t p, uint32_t g, uint32_t q0) {
+    const uint32_t i = g & kPeIndex;
+    const uint32_t s = q.pre[p * q.cap + (i ? min<uint64_t>(i - 1u, q.cap - 1u) : 0u)];
+    return (g & kPeNoneBefore) ? q0 : s;
 }
 
 // The class maps of the launch's properties, one table word per thread
@@ -324,8 +364,8 @@ __device__ __forceinline__ void block_scan(uint32_t P, const BMap<MW>* f, const 
 
 }  // namespace
 
-template <int PMAX, int MW, int ITEMS>
-__global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a) {
+template <int PMAX, int MW, int ITEMS, bool PE>
+__global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a, PeParam<PE> q) {
     constexpr uint32_t TILE = kMsThreads * ITEMS;
     __shared__ uint32_t s_cm[PMAX][16][MW];
     __shared__ uint32_t s_q0[PMAX];
@@ -341,7 +381,37 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a) {
     if (!a.read_desc && a.desc && r.cnt) store_desc<ITEMS>(a, my0, r);
     __syncthreads();
     BMap<MW> f[PMAX], excl[PMAX], tot[PMAX];
-    run_maps<PMAX, MW, ITEMS>(r, a.n_props, s_cm, s_q0, f);
+    if constexpr (PE) {
+        const Bounds bd = load_bounds(q, my0, r);
+        const uint32_t last = r.m_head ? 31u - (uint32_t)__clz(r.m_head) : 0u;
+        const uint32_t from = r.m_head ? ~((2u << last) - 1u) : kAll;          // what follows the last head
+        const uint32_t gl = q.bound[r.m_head ? my0 + last : 0];
+        uint32_t start_q[PMAX];
+#pragma unroll
+        for (int p = 0; p < PMAX; ++p)
+            start_q[p] = p < (int)a.n_props ? pe_start(q, prop_index<PMAX>(a, p), gl, s_q0[p]) : 0u;
+        if ((bd.gaps & from) == 0) {
+            run_maps<PMAX, MW, ITEMS>(r, a.n_props, s_cm, start_q, f);
+        } else {
+            // parent entries inside an instance: word by word, their range's map first
+            const uint64_t* par = q.words + *q.n_own;
+#pragma unroll
+            for (int p = 0; p < PMAX; ++p) f[p] = r.m_head ? bm_const<MW>(start_q[p]) : bm_identity<MW>();
+#pragma unroll 1
+            for (uint32_t j = last; j < r.cnt; ++j) {
+                const bool gap = (bd.gaps >> j) & 1u;
+                const uint32_t hi = q.bound[my0 + j] & kPeIndex, lo = gap ? q.bound[my0 + j - 1] & kPeIndex : hi;
+#pragma unroll
+                for (int p = 0; p < PMAX; ++p) {
+                    if (p >= (int)a.n_props) continue;
+                    if (gap) f[p] = bm_compose<MW>(pe_range<MW>(q, s_cm[p], par, prop_index<PMAX>(a, p), lo, hi), f[p]);
+                    f[p] = bm_compose<MW>(bm_load<MW>(s_cm[p][run_class(r, (int)j)]), f[p]);
+                }
+            }
+        }
+    } else {
+        run_maps<PMAX, MW, ITEMS>(r, a.n_props, s_cm, s_q0, f);
+    }
     uint32_t cnt[4], cexcl[4], ctot[4];
     cnt[0] = __popc(r.m_head);
 #pragma unroll
@@ -497,8 +567,8 @@ __global__ __launch_bounds__(kSpineThreads) void k_ms_spine(ScanArgs a) {
 
 // TL: the instantiation that also walks the verdict timeline (its registers
 // stay out of the plain sweep's occupancy)
-template <int PMAX, int MW, int ITEMS, bool TL>
-__global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a) {
+template <int PMAX, int MW, int ITEMS, bool TL, bool PE>
+__global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> q) {
     constexpr uint32_t TILE = kMsThreads * ITEMS;
     constexpr bool kParents = PMAX <= 4;         // LDS room to stage parent ids
     constexpr uint32_t kIvStride = TILE + 1;
@@ -567,8 +637,44 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a) {
     for (int p = 0; p < PMAX; ++p)
 #pragma unroll
         for (int h = 0; h < ITEMS / 16; ++h) st[p][h] = 0;
+    if constexpr (PE) {
+        const Bounds bd = load_bounds(q, my0, r);
+        if (bd.gaps != 0) {
+            // parent entries inside an instance: word by word
+            const uint64_t* par = q.words + *q.n_own;
+#pragma unroll 1
+            for (uint32_t j = 0; j < r.cnt; ++j) {
+                const bool hd = (r.m_head >> j) & 1u, gap = (bd.gaps >> j) & 1u;
+                const uint32_t g = q.bound[my0 + j], hi = g & kPeIndex, lo = gap ? q.bound[my0 + j - 1] & kPeIndex : hi;
+#pragma unroll
+                for (int p = 0; p < PMAX; ++p) {
+                    if (p >= (int)P) continue;
+                    const uint32_t pi = prop_index<PMAX>(a, p);
+                    if (hd) cur[p] = pe_start(q, pi, g, s_q0[p]);
+                    else if (gap) cur[p] = bm_at<MW>(pe_range<MW>(q, s_cm[p], par, pi, lo, hi), cur[p]);
+                    cur[p] = bm_at<MW>(bm_load<MW>(s_cm[p][run_class(r, (int)j)]), cur[p]);
+                    st[p][0] |= (uint64_t)cur[p] << (4 * j);
+                }
+            }
+        } else {
+#pragma clang loop unroll(full)
+            for (int p = 0; p < PMAX; ++p) {
+                if (p >= (int)P) continue;
+                const uint32_t pi = prop_index<PMAX>(a, p);
+                uint32_t start[16];
+#pragma clang loop unroll(full)
+                for (int j = 0; j < 16; ++j) start[j] = pe_start(q, pi, bd.g[j], s_q0[p]);
+#pragma clang loop unroll(full)
+                for (int j = 0; j < 16; ++j) {
+                    cur[p] = bm_at<MW>(bm_load<MW>(s_cm[p][run_class(r, j)]), ((r.m_head >> j) & 1u) ? start[j] : cur[p]);
+                    st[p][0] |= (uint64_t)cur[p] << (4 * j);
+                }
+            }
+        }
+    }
 #pragma clang loop unroll(full)
     for (int j = 0; j < ITEMS; ++j) {
+        if (PE) break;
         const uint32_t c = run_class(r, j);
         const bool hd = (r.m_head >> j) & 1u;
 #pragma clang loop unroll(full)
@@ -593,8 +699,16 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a) {
                 // the choice is not turned into an indexed register array
                 uint32_t s0 = (uint32_t)(st[p][0] >> sh) & 15u, s1 = (uint32_t)(st[p][ITEMS / 16 - 1] >> sh) & 15u;
                 asm("" : "+v"(s0), "+v"(s1));
-                const uint32_t q = ITEMS > 16 && j >= 16u ? s1 : s0;
-                s_iv[p * kIvStride + slot] = (s_lab[p][q >> 3] >> (4 * (q & 7u))) & 15u;
+                uint32_t qe = ITEMS > 16 && j >= 16u ? s1 : s0;
+                if constexpr (PE) {
+                    // the parent's entries after the instance's last own event
+                    const uint32_t g = q.bound[my0 + j];
+                    if (!(g & kPeNoneAfter)) {
+                        const uint2 m = q.suf[prop_index<PMAX>(a, p) * q.cap + (g & kPeIndex)];
+                        qe = ((qe & 8u ? m.y : m.x) >> (4 * (qe & 7u))) & 15u;
+                    }
+                }
+                s_iv[p * kIvStride + slot] = (s_lab[p][qe >> 3] >> (4 * (qe & 7u))) & 15u;
             }
             if (kParents && L >= 2) s_par[slot] = (uint16_t)(par_local + __popc(m_par & upto));
             my_lo = min(my_lo, (uint32_t)id);
@@ -803,13 +917,13 @@ hipError_t launch_event_unpack(const ScanArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int PMAX, int MW, int ITEMS>
-static void launch_ms_t(const ScanArgs& a, hipStream_t s) {
+template <int PMAX, int MW, int ITEMS, bool PE>
+static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) {
     const uint32_t tiles = (uint32_t)((a.n + kMsThreads * ITEMS - 1) / (kMsThreads * ITEMS));
     const dim3 grid(tiles ? tiles : 1);
     ScanArgs r = a;
     r.tiles = tiles;
-    hipLaunchKernelGGL((k_ms_reduce<PMAX, MW, ITEMS>), grid, dim3(kMsThreads), 0, s, r);
+    hipLaunchKernelGGL((k_ms_reduce<PMAX, MW, ITEMS, PE>), grid, dim3(kMsThreads), 0, s, r, q);
     // one spine block takes kSpineThreads x chunk records per pass; beyond two
     // passes the chunks are spread over blocks
     constexpr uint32_t kPass = (uint32_t)kSpineThreads * spine_chunk_items<4 + PMAX * MW>();
@@ -824,32 +938,39 @@ static void launch_ms_t(const ScanArgs& a, hipStream_t s) {
     }
     ScanArgs d = r;
     d.read_desc = 1;
-    if (a.inst_conc || a.event_pack) hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, true>), grid, dim3(kMsThreads), 0, s, d);
-    else hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, false>), grid, dim3(kMsThreads), 0, s, d);
+    if constexpr (!PE) {
+        if (a.inst_conc || a.event_pack) {
+            hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, true, false>), grid, dim3(kMsThreads), 0, s, d, q);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, false, PE>), grid, dim3(kMsThreads), 0, s, d, q);
 }
 
-template <int ITEMS>
-static void launch_ms_items(const ScanArgs& a, hipStream_t s) {
+template <int ITEMS, bool PE>
+static void launch_ms_items(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) {
     if (a.max_states <= 8) {
-        if (a.n_props <= 1) launch_ms_t<1, 2, ITEMS>(a, s);
-        else if (a.n_props <= 2) launch_ms_t<2, 2, ITEMS>(a, s);
-        else if (a.n_props <= 4) launch_ms_t<4, 2, ITEMS>(a, s);
-        else launch_ms_t<8, 2, ITEMS>(a, s);
+        if (a.n_props <= 1) launch_ms_t<1, 2, ITEMS, PE>(a, q, s);
+        else if (a.n_props <= 2) launch_ms_t<2, 2, ITEMS, PE>(a, q, s);
+        else if (a.n_props <= 4) launch_ms_t<4, 2, ITEMS, PE>(a, q, s);
+        else launch_ms_t<8, 2, ITEMS, PE>(a, q, s);
     } else {
-        if (a.n_props <= 1) launch_ms_t<1, 4, ITEMS>(a, s);
-        else if (a.n_props <= 2) launch_ms_t<2, 4, ITEMS>(a, s);
-        else launch_ms_t<4, 4, ITEMS>(a, s);
+        if (a.n_props <= 1) launch_ms_t<1, 4, ITEMS, PE>(a, q, s);
+        else if (a.n_props <= 2) launch_ms_t<2, 4, ITEMS, PE>(a, q, s);
+        else launch_ms_t<4, 4, ITEMS, PE>(a, q, s);
     }
 }
 
-// items: words per thread, 16 (4,096-word tiles) or 32 (8,192-word tiles).
-// The workspace arrays are sized for 16 (the more tiles).
-hipError_t launch_mapscan(const ScanArgs& a, int items, hipStream_t s) {
+// items: words per thread, 16 (4,096-word tiles) or 32 (8,192-word tiles; not
+// with parent events).  The workspace arrays are sized for 16 (the more tiles).
+hipError_t launch_mapscan(const ScanArgs& a, int items, const ParentArgs* pe, hipStream_t s) {
     if (a.n_props < 1 || a.n_props > (a.max_states <= 8 ? 8u : 4u) || (a.structure && a.n_props > 4) || !a.n_dev ||
-        !a.desc || !a.agg || !a.prefix || !a.trec || (items != 16 && items != 32))
+        !a.desc || !a.agg || !a.prefix || !a.trec || (items != 16 && items != 32) ||
+        (pe && (items != 16 || a.inst_conc || a.event_pack)))
         return hipErrorInvalidValue;
-    if (items == 16) launch_ms_items<16>(a, s);
-    else launch_ms_items<32>(a, s);
+    if (pe) launch_ms_items<16, true>(a, *pe, s);
+    else if (items == 16) launch_ms_items<16, false>(a, NoParent{}, s);
+    else launch_ms_items<32, false>(a, NoParent{}, s);
     return hipGetLastError();
 }
 

@@ -201,9 +201,9 @@ struct WsLayout {
     uint64_t ms_desc_off, ms_agg_off, ms_prefix_off, ms_trec_off, ms_chunk_off;   // the split map scan
     uint32_t ms_tiles;
     // parent events
-    uint64_t pe_tree_off, pe_trec_off, pe_samples_off, pe_tile_agg_off, pe_tile_prefix_off, pe_tile_heads_off, pe_tile_hprefix_off;
+    uint64_t pe_tree_off, pe_pre_off, pe_suf_off;
     uint64_t pe_tree_lvl[kPeMaxTreeLevels], pe_tree_cnt[kPeMaxTreeLevels];
-    uint32_t pe_levels, pe_tiles;
+    uint32_t pe_levels;
 };
 
 // Properties share scan launches by monitor size: up to 8 whose monitors have
@@ -305,7 +305,8 @@ WsLayout plan_workspace(const ltl4c_layout& L, const Geometry& g, uint64_t n, ui
     }
     if (g.parent) {
         // the segment tree over the parent events (levels 1 .. ceil(log2 n),
-        // per property), and the tile aggregates and prefixes
+        // per property), and every entry's prefix state and suffix map; the
+        // own events' bounds share inst_start (no timeline with parent events)
         w.pe_levels = 0;
         uint64_t nodes = 0;
         for (uint32_t lv = 1; lv < (uint32_t)kPeMaxTreeLevels && (1ull << (lv - 1)) < n; ++lv) {
@@ -314,15 +315,9 @@ WsLayout plan_workspace(const ltl4c_layout& L, const Geometry& g, uint64_t n, ui
             nodes += (uint64_t)P * w.pe_tree_cnt[lv];
             w.pe_levels = lv;
         }
-        w.pe_tree_off = off; off = align256(off + 16 * std::max<uint64_t>(nodes, 1));
-        w.pe_tiles = (uint32_t)((n + kPeTile - 1) / kPeTile);
-        const uint64_t t = std::max<uint32_t>(w.pe_tiles, 1);
-        w.pe_tile_agg_off = off;     off = align256(off + 16 * t * P);
-        w.pe_tile_prefix_off = off;  off = align256(off + 16 * t * P);
-        w.pe_trec_off = off;         off = align256(off + 16 * t * kPeThreads * P);
-        w.pe_samples_off = off;      off = align256(off + 8 * kPeSamples);
-        w.pe_tile_heads_off = off;   off = align256(off + 4 * t);
-        w.pe_tile_hprefix_off = off; off = align256(off + 4 * t);
+        w.pe_tree_off = off; off = align256(off + 8 * std::max<uint64_t>(nodes, 1));
+        w.pe_pre_off = off;  off = align256(off + (uint64_t)P * n);
+        w.pe_suf_off = off;  off = align256(off + 8 * (uint64_t)P * n);
     }
     w.total = off;
     return w;
@@ -1064,18 +1059,6 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
         if (s) return s;
     }
 
-    // parent events: the own events are the first n_own sorted words
-    uint32_t* n_own = g.parent ? z + w.n_valid_off + 2 : nullptr;
-    ParentArgs pa{};
-    if (g.parent && n > 0) {
-        pa.words = sorted;
-        pa.n_kept = z + w.n_valid_off;
-        pa.n_par = z + w.n_valid_off + 1;
-        pa.n_own = n_own;
-        s = launch(ctx, "parent", [&] { return launch_parent_counts(pa, st); });
-        if (s) return s;
-    }
-
     // per-instance arrays: the verdicts always exist (caller's or workspace)
     uint8_t* inst_verdict = out->inst_verdict ? out->inst_verdict : ws + w.inst_verdict_off;
     const uint64_t inst_stride = out->inst_verdict ? out->capacity : std::max<uint64_t>(n, 1);
@@ -1110,7 +1093,7 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
         ScanArgs sa{};
         sa.words = sorted;
         sa.n = (uint32_t)n;
-        sa.n_dev = g.parent ? n_own : g.compact ? z + w.n_valid_off : nullptr;   // the first radix pass dropped excluded events
+        sa.n_dev = g.parent ? z + w.n_valid_off + 2 : g.compact ? z + w.n_valid_off : nullptr;   // the first radix pass dropped excluded events
         sa.cbits = g.cbits + g.ibits;                        // where the key starts
         sa.class_mask = (1u << g.cbits) - 1u;
         sa.index_shift = g.cbits;
@@ -1138,7 +1121,7 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
             sa.inst_conc = out->inst_conclusive;
             sa.inst_start = inst_start;
         }
-        const bool split = ctx->scan_variant == kSplitScanVariant || ctx->scan_variant == kSplitScanVariant32;
+        const bool split = g.parent || ctx->scan_variant == kSplitScanVariant || ctx->scan_variant == kSplitScanVariant32;
         uint8_t* pack = nullptr;
         if (out->event_verdict) {
             sa.event_verdict = out->event_verdict;
@@ -1159,8 +1142,8 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
         // one launch per property group, each with its own look-back rows and
         // ticket; the first one also writes the numbering
         // The split map scan (reduce, spine, down sweep; its down sweep also
-        // writes the verdict timeline on request).  With parent events it
-        // numbers the own events (the verdicts come after).
+        // writes the verdict timeline on request).  With parent events it runs
+        // over the own events and merges the parent events in.
         if (split) {
             if (!sa.n_dev) {
                 // nothing is excluded: every word counts
@@ -1176,8 +1159,41 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
             sa.chunk_pre = sa.chunk_agg + (uint64_t)kMsRec * (w.ms_tiles / kMsSpineThreads + 1);
             sa.tiles = w.ms_tiles;
         }
-        // (with parent events only the numbering launch: the verdicts come after)
-        for (size_t gi = 0; gi < (g.parent ? 1 : groups.size()); ++gi) {
+        ParentArgs pa{};
+        if (g.parent) {
+            pa.words = sorted;
+            pa.n_par = z + w.n_valid_off + 1;
+            pa.n_own = z + w.n_valid_off + 2;
+            pa.cbits = g.cbits;
+            pa.class_mask = (1u << g.cbits) - 1u;
+            pa.ibits = g.ibits;
+            pa.index_mask = g.ibits ? (1ull << g.ibits) - 1ull : 0ull;
+            pa.prefix_shift = g.cbits + g.ibits + L.key_bits[L.n_keys - 1];
+            const uint32_t pbits = g.key_bits_total - g.stream_bits - L.key_bits[L.n_keys - 1];
+            pa.prefix_mask = pbits ? (1ull << pbits) - 1ull : 0ull;
+            pa.n_props = P;
+            pa.plan = plan;
+            pa.tree = reinterpret_cast<uint2*>(ws + w.pe_tree_off);
+            for (uint32_t lv = 1; lv <= w.pe_levels; ++lv) {
+                pa.tree_off[lv] = w.pe_tree_lvl[lv];
+                pa.tree_cnt[lv] = w.pe_tree_cnt[lv];
+            }
+            pa.bound = inst_start;
+            pa.cap = n;
+            pa.pre = ws + w.pe_pre_off;
+            pa.suf = reinterpret_cast<uint2*>(ws + w.pe_suf_off);
+            for (uint32_t l0 = 0; l0 < w.pe_levels; l0 += kPeTreeLevelsPerLaunch) {
+                const uint32_t nlev = std::min<uint32_t>(kPeTreeLevelsPerLaunch, w.pe_levels - l0);
+                const uint64_t nodes0 = l0 ? w.pe_tree_cnt[l0] : n;
+                s = launch(ctx, "parent", [&] { return launch_parent_tree(pa, l0, nlev, nodes0, st); });
+                if (s) return s;
+            }
+            s = launch(ctx, "parent", [&] { return launch_parent_affix(pa, n, st); });
+            if (s) return s;
+            s = launch(ctx, "parent", [&] { return launch_parent_bounds(pa, n, st); });
+            if (s) return s;
+        }
+        for (size_t gi = 0; gi < groups.size(); ++gi) {
             sa.n_props = groups[gi].cnt;
             std::memcpy(sa.prop_idx, groups[gi].idx, sizeof sa.prop_idx);
             sa.max_states = groups[gi].states;
@@ -1191,8 +1207,8 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
                     s = launch(ctx, "fill", [&] { return launch_fill_u8(pack, (uint8_t)0xFF, (sa.n_props <= 4 ? 2 : 4) * n, st); });
                     if (s) return s;
                 }
-                const int items = ctx->scan_variant == kSplitScanVariant32 ? 32 : 16;
-                s = launch(ctx, "scan", [&] { return launch_mapscan(sa, items, st); });
+                const int items = ctx->scan_variant == kSplitScanVariant32 && !g.parent ? 32 : 16;
+                s = launch(ctx, "scan", [&] { return launch_mapscan(sa, items, g.parent ? &pa : nullptr, st); });
                 if (s == LTL4C_OK && pack) s = launch(ctx, "timeline", [&] { return launch_event_unpack(sa, st); });
             } else {
                 s = launch(ctx, "scan", [&] { return launch_scan(sa, ctx->scan_variant, st); });
@@ -1200,48 +1216,6 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
             if (s) return s;
         }
 
-        if (g.parent) {
-            // every instance's verdict with its parent events merged in
-            pa.cbits = g.cbits;
-            pa.class_mask = (1u << g.cbits) - 1u;
-            pa.ibits = g.ibits;
-            pa.index_mask = g.ibits ? (1ull << g.ibits) - 1ull : 0ull;
-            pa.key_shift = g.cbits + g.ibits;
-            pa.prefix_shift = pa.key_shift + L.key_bits[L.n_keys - 1];
-            const uint32_t pbits = g.key_bits_total - g.stream_bits - L.key_bits[L.n_keys - 1];
-            pa.prefix_mask = pbits ? (1ull << pbits) - 1ull : 0ull;
-            pa.n_props = P;
-            pa.plan = plan;
-            pa.tree = reinterpret_cast<uint4*>(ws + w.pe_tree_off);
-            for (uint32_t lv = 1; lv <= w.pe_levels; ++lv) {
-                pa.tree_off[lv] = w.pe_tree_lvl[lv];
-                pa.tree_cnt[lv] = w.pe_tree_cnt[lv];
-            }
-            pa.tile_agg = reinterpret_cast<uint4*>(ws + w.pe_tile_agg_off);
-            pa.tile_prefix = reinterpret_cast<uint4*>(ws + w.pe_tile_prefix_off);
-            pa.trec = reinterpret_cast<uint4*>(ws + w.pe_trec_off);
-            pa.samples = reinterpret_cast<uint64_t*>(ws + w.pe_samples_off);
-            pa.tile_heads = reinterpret_cast<uint32_t*>(ws + w.pe_tile_heads_off);
-            pa.tile_head_prefix = reinterpret_cast<uint32_t*>(ws + w.pe_tile_hprefix_off);
-            pa.inst_verdict = inst_verdict;
-            pa.inst_stride = inst_stride;
-            pa.inst_limit = inst_stride;
-            pa.err = ctx->err_dev;
-            s = launch(ctx, "parent", [&] { return launch_parent_samples(pa, st); });
-            if (s) return s;
-            for (uint32_t l0 = 0; l0 < w.pe_levels; l0 += kPeTreeLevelsPerLaunch) {
-                const uint32_t nlev = std::min<uint32_t>(kPeTreeLevelsPerLaunch, w.pe_levels - l0);
-                const uint64_t nodes0 = l0 ? w.pe_tree_cnt[l0] : n;
-                s = launch(ctx, "parent", [&] { return launch_parent_tree(pa, l0, nlev, nodes0, st); });
-                if (s) return s;
-            }
-            s = launch(ctx, "parent", [&] { return launch_parent_pass(pa, false, w.pe_tiles, st); });
-            if (s) return s;
-            s = launch(ctx, "parent", [&] { return launch_parent_spine(pa, st); });
-            if (s) return s;
-            s = launch(ctx, "parent", [&] { return launch_parent_pass(pa, true, w.pe_tiles, st); });
-            if (s) return s;
-        }
         if (out->inst_conclusive) {
             InstConclusiveArgs ia{};
             ia.inst_conc = out->inst_conclusive;
