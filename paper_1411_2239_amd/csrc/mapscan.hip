@@ -575,7 +575,10 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
     __shared__ uint32_t s_cm[PMAX][16][MW];
     __shared__ uint32_t s_q0[PMAX], s_lab[PMAX][2];
     __shared__ uint32_t s_red[2][kMsThreads / 64];
-    // staging: verdict bytes [P][tile + 1], then 16-bit parent offsets [tile + 1]
+    // staging: verdict bytes [P][tile + 1], then 16-bit parent offsets [tile + 1];
+    // with keys asked for, the last word of every instance too (dynamic, so
+    // that calls without keys keep the blocks per CU)
+    extern __shared__ uint16_t s_pos[];
     __shared__ uint32_t s_stage[(PMAX * kIvStride + 3) / 4 + (kParents ? (kIvStride + 1) / 2 : 0)];
     const uint32_t n = *a.n_dev;
     const uint64_t base = (uint64_t)blockIdx.x * TILE;
@@ -713,7 +716,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
             if (kParents && L >= 2) s_par[slot] = (uint16_t)(par_local + __popc(m_par & upto));
             my_lo = min(my_lo, (uint32_t)id);
             my_hi = max(my_hi, (uint32_t)id + 1u);
-            if (structure && a.inst_keys) a.inst_keys[id] = a.words[my0 + j] >> a.cbits;
+            if (structure && a.inst_keys) s_pos[slot] = (uint16_t)(tid * ITEMS + j);
         } else {
             err |= kErrCapacity;
         }
@@ -856,6 +859,11 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
                 a.inst_verdict[a.prop_idx[p] * a.inst_stride + lo + i] = s_iv[p * kIvStride + slot0 + i];
         if (structure && a.inst_parent && L >= 2)
             for (uint32_t i = tid; i < cnt_iv; i += kMsThreads) a.inst_parent[lo + i] = par_tile + s_par[slot0 + i];
+        // the keys in one stream as well: 10M events with 2.9M instances and
+        // parent events took 112 us with each key written where its instance
+        // ends, 60 us so
+        if (structure && a.inst_keys)
+            for (uint32_t i = tid; i < cnt_iv; i += kMsThreads) a.inst_keys[lo + i] = a.words[base + s_pos[slot0 + i]] >> a.cbits;
     }
     // the thread holding the last word publishes the totals
     if (structure && r.cnt && my0 + r.cnt == n) {
@@ -938,13 +946,14 @@ static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) 
     }
     ScanArgs d = r;
     d.read_desc = 1;
+    const uint32_t lds = a.structure && a.inst_keys ? 2u * (kMsThreads * ITEMS + 1) : 0u;
     if constexpr (!PE) {
         if (a.inst_conc || a.event_pack) {
-            hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, true, false>), grid, dim3(kMsThreads), 0, s, d, q);
+            hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, true, false>), grid, dim3(kMsThreads), lds, s, d, q);
             return;
         }
     }
-    hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, false, PE>), grid, dim3(kMsThreads), 0, s, d, q);
+    hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, false, PE>), grid, dim3(kMsThreads), lds, s, d, q);
 }
 
 template <int ITEMS, bool PE>
