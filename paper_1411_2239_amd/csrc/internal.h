@@ -223,6 +223,8 @@ struct ZeroArgs {
     uint64_t mult;
     uint64_t n_words;                    // used when n_dev is null
     uint64_t limit;
+    uint32_t* also;                      // a second, short range (at most 256 words)
+    uint32_t n_also;
 };
 
 
@@ -265,6 +267,7 @@ struct GroupState {
     uint32_t* err;
 };
 
+constexpr int kGroupThreads = 1024;
 struct GroupUpdateArgs {
     GroupState g;
     const uint32_t* n_seg;               // segments (instances) of this push

@@ -149,6 +149,7 @@ __global__ __launch_bounds__(256) void k_zero(ZeroArgs a) {
     uint4* p4 = reinterpret_cast<uint4*>(a.ptr);
     for (uint64_t i = t0; i < head; i += stride) p4[i] = make_uint4(0u, 0u, 0u, 0u);
     for (uint64_t i = head * 4 + t0; i < n; i += stride) a.ptr[i] = 0u;
+    if (t0 < a.n_also) a.also[t0] = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -1403,11 +1404,14 @@ __device__ uint64_t table_slot(uint64_t* keys, uint32_t stride, uint64_t mask, u
 }
 
 // Put node `slot` of `level` on the level's dirty list once.  Called by every
-// lane of a wave (want: this lane has a node to mark); the appends of a wave
-// share one atomic on the list length.  A dirty flag only goes from 0 to 1
-// within a kernel, so a cached read of 1 is final and skips the exchange.
-__device__ __forceinline__ void mark_nodes(const GroupState& g, uint32_t level, bool want, uint32_t slot) {
-    const int lane = threadIdx.x & 63;
+// thread of a block (want: this thread has a node to mark); the appends of a
+// block share one atomic on the list length (s_cnt: one word per wave, and the
+// base).  A dirty flag only goes from 0 to 1 within a kernel, so a cached read
+// of 1 is final and skips the exchange.
+template <int WAVES>
+__device__ __forceinline__ void mark_nodes(const GroupState& g, uint32_t level, bool want, uint32_t slot,
+                                           uint32_t* s_cnt /*[WAVES + 1]*/) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint32_t* dirty = level == 0 ? g.rdirty : g.ndirty[level];
     uint32_t* list = level == 0 ? g.rlist : g.nlist[level];
     bool mine = false;
@@ -1415,12 +1419,17 @@ __device__ __forceinline__ void mark_nodes(const GroupState& g, uint32_t level, 
         mine = __hip_atomic_load(dirty + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u &&
                atomicExch(dirty + slot, 1u) == 0u;
     const uint64_t m = __ballot(mine);
-    if (m == 0) return;
-    const int leader = __ffsll((unsigned long long)m) - 1;
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(g.list_cnt + level, (uint32_t)__popcll(m));
-    base = __shfl(base, leader, 64);
-    if (mine) list[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = slot;
+    if (lane == 0) s_cnt[w] = (uint32_t)__popcll(m);
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < WAVES; ++i) {
+        before += i < w ? s_cnt[i] : 0u;
+        total += s_cnt[i];
+    }
+    if (threadIdx.x == 0 && total) s_cnt[WAVES] = atomicAdd(g.list_cnt + level, total);
+    __syncthreads();
+    if (mine) list[s_cnt[WAVES] + before + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = slot;
 }
 
 __device__ __forceinline__ uint32_t* counts_of(const GroupState& g, uint32_t level, uint32_t slot, uint32_t p) {
@@ -1431,7 +1440,12 @@ __device__ __forceinline__ uint32_t* counts_of(const GroupState& g, uint32_t lev
 // One thread per binding segment of the pushed chunks.  Segments are in key
 // order, so the lanes of a wave whose bindings share a parent node form a
 // run: its count changes are summed by ballots and applied once per run.
-__global__ __launch_bounds__(256) void k_group_update(GroupUpdateArgs a) {
+// Large blocks, because every block appends to one dirty list.  0.6M segments
+// of bindings that are all known take 42.5 us (of fresh ones 122 us): random
+// reads and writes of a 268 MB table; reading four slots of a probe at once
+// (fewer trips, more lines) took 47 us.
+__global__ __launch_bounds__(kGroupThreads) void k_group_update(GroupUpdateArgs a) {
+    __shared__ uint32_t s_mark[kGroupThreads / 64 + 1];
     const GroupState& g = a.g;
     const uint32_t nseg = *a.n_seg;
     const uint32_t L = g.n_levels;
@@ -1552,12 +1566,13 @@ __global__ __launch_bounds__(256) void k_group_update(GroupUpdateArgs a) {
             }
         }
         if (ok) g.bslot[2 * b + 1] = aux_new;
-        mark_nodes(g, plevel, head && touched_run, parent);
+        mark_nodes<kGroupThreads / 64>(g, plevel, head && touched_run, parent, s_mark);
     }
 }
 
 // Re-valuate the dirty nodes of one level (>= 1) and pass changed verdicts up.
 __global__ __launch_bounds__(256) void k_group_level(GroupState g, uint32_t level) {
+    __shared__ uint32_t s_mark[256 / 64 + 1];
     const uint32_t n = g.list_cnt[level];
     for (uint32_t base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
         const uint32_t i = base + threadIdx.x;
@@ -1579,7 +1594,7 @@ __global__ __launch_bounds__(256) void k_group_level(GroupState g, uint32_t leve
                 touched = true;
             }
         }
-        mark_nodes(g, level - 1, touched, parent);
+        mark_nodes<256 / 64>(g, level - 1, touched, parent, s_mark);
     }
 }
 
@@ -1917,9 +1932,9 @@ hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
 namespace ltl4c {
 
 hipError_t launch_group_update(const GroupUpdateArgs& a, uint64_t max_seg, hipStream_t s) {
-    const uint64_t want = (max_seg + 255) / 256;
-    const uint32_t blocks = (uint32_t)(want < 2048 ? (want ? want : 1) : 2048);
-    hipLaunchKernelGGL(k_group_update, dim3(blocks), dim3(256), 0, s, a);
+    const uint64_t want = (max_seg + kGroupThreads - 1) / kGroupThreads;
+    const uint32_t blocks = (uint32_t)(want < 4096 ? (want ? want : 1) : 4096);
+    hipLaunchKernelGGL(k_group_update, dim3(blocks), dim3(kGroupThreads), 0, s, a);
     return hipGetLastError();
 }
 

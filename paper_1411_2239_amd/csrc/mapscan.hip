@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a, PeParam<PE
     __shared__ uint32_t s_q0[PMAX];
     __shared__ uint32_t s_wm[PMAX][kMsThreads / 64 + 1][MW];
     __shared__ uint32_t s_wc[4][kMsThreads / 64 + 1];
-    const uint32_t n = *a.n_dev;
+    const uint32_t n = a.n_dev ? *a.n_dev : a.n;
     const uint64_t base = (uint64_t)blockIdx.x * TILE;
     if (base >= n) return;                       // the whole block: no word of this tile
     const uint64_t my0 = base + (uint64_t)threadIdx.x * ITEMS;
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(kSpineThreads) void k_ms_spine(ScanArgs a) {
     __shared__ uint32_t s_wm[PMAX][kSpineThreads / 64 + 1][MW];
     __shared__ uint32_t s_wc[4][kSpineThreads / 64 + 1];
     __shared__ uint32_t s_carry[NW];
-    const uint32_t n = *a.n_dev;
+    const uint32_t n = a.n_dev ? *a.n_dev : a.n;
     const uint32_t tiles = (n + TILE - 1) / TILE;
     const uint32_t P = a.n_props;
     const uint32_t nchunks = MODE == 0 ? 1u : (tiles + a.spine_chunk - 1) / a.spine_chunk;
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
     // that calls without keys keep the blocks per CU)
     extern __shared__ uint16_t s_pos[];
     __shared__ uint32_t s_stage[(PMAX * kIvStride + 3) / 4 + (kParents ? (kIvStride + 1) / 2 : 0)];
-    const uint32_t n = *a.n_dev;
+    const uint32_t n = a.n_dev ? *a.n_dev : a.n;
     const uint64_t base = (uint64_t)blockIdx.x * TILE;
     if (base >= n) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -711,7 +711,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
                         qe = ((qe & 8u ? m.y : m.x) >> (4 * (qe & 7u))) & 15u;
                     }
                 }
-                s_iv[p * kIvStride + slot] = (s_lab[p][qe >> 3] >> (4 * (qe & 7u))) & 15u;
+                s_iv[p * kIvStride + slot] = a.emit_state ? qe : (s_lab[p][qe >> 3] >> (4 * (qe & 7u))) & 15u;
             }
             if (kParents && L >= 2) s_par[slot] = (uint16_t)(par_local + __popc(m_par & upto));
             my_lo = min(my_lo, (uint32_t)id);
@@ -973,7 +973,7 @@ static void launch_ms_items(const ScanArgs& a, const PeParam<PE>& q, hipStream_t
 // items: words per thread, 16 (4,096-word tiles) or 32 (8,192-word tiles; not
 // with parent events).  The workspace arrays are sized for 16 (the more tiles).
 hipError_t launch_mapscan(const ScanArgs& a, int items, const ParentArgs* pe, hipStream_t s) {
-    if (a.n_props < 1 || a.n_props > (a.max_states <= 8 ? 8u : 4u) || (a.structure && a.n_props > 4) || !a.n_dev ||
+    if (a.n_props < 1 || a.n_props > (a.max_states <= 8 ? 8u : 4u) || (a.structure && a.n_props > 4) ||
         !a.desc || !a.agg || !a.prefix || !a.trec || (items != 16 && items != 32) ||
         (pe && (items != 16 || a.inst_conc || a.event_pack)))
         return hipErrorInvalidValue;

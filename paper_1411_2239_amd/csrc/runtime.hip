@@ -150,6 +150,7 @@ struct Geometry {
     bool excl;
     uint32_t prefix_bits[kMaxLevels];       // bits of the packed prefix that identifies a level-m node
     bool parent;                            // parent events: a kind bit above the keys (1 = parent event)
+    bool no_timeline;                       // no room for the verdict timeline in the workspace (stream groups)
 };
 
 // stream_is_level: the id above the keys is a tree level of its own (batches
@@ -286,7 +287,7 @@ WsLayout plan_workspace(const ltl4c_layout& L, const Geometry& g, uint64_t n, ui
         w.inst_parent_off = off;
         off = align256(off + 4 * n);
     }
-    w.inst_start_off = off; off = align256(off + 4 * n);   // verdict timeline, when asked for
+    w.inst_start_off = off; off = align256(off + (g.no_timeline ? 0 : 4 * n));   // verdict timeline, when asked for
     // split map scan: a descriptor byte per word, a record per tile and its prefix
     w.ms_tiles = (uint32_t)((n + kMsTileMin - 1) / kMsTileMin);
     w.ms_desc_off = off;   off = align256(off + n + 64);
@@ -655,7 +656,8 @@ struct GroupHost {
     uint64_t state_bytes = 0;
     uint8_t* ws = nullptr;
     uint64_t ws_bytes = 0;
-    WsLayout w{};
+    Geometry g1{};                     // g with one level: the scan of a push numbers segments only
+    WsLayout w{};                      // for max_batch events; a push plans its own size inside it
     uint64_t seg_keys_off = 0;         // inside ws, after the eval workspace
     GroupState gs{};
     uint32_t* chunk_dev = nullptr;     // [kMaxChunks + 1 offsets][kMaxChunks streams]
@@ -751,22 +753,26 @@ int32_t group_configure(ltl4c_ctx* ctx, GroupHost& G, const int32_t* props, int3
     if (G.V > (uint32_t)kMaxProps)
         return fail(LTL4C_EUNSUPPORTED, "a stream group takes properties whose monitors have 16 states in total");
     const uint32_t sb = std::max<uint32_t>(1, bits_for(max_streams));
-    G.g = geometry(L, sb, false, false, sort_threads(ctx->sort_variant) >= 512);
+    // (the look-back scan takes excluded events sorted behind the others, the
+    // split scan without them)
+    const bool split = ctx->scan_variant == kSplitScanVariant || ctx->scan_variant == kSplitScanVariant32;
+    G.g = geometry(L, sb, false, split, sort_threads(ctx->sort_variant) >= 512);
     if (G.g.cbits + G.g.key_bits_total + (G.g.excl ? 1 : 0) > 63)
         return fail(LTL4C_EUNSUPPORTED, "stream id, keys and class bits exceed 63 bits");
     G.sort_variant = ctx->sort_variant;
     G.scan_variant = ctx->scan_variant;
     G.lay_ws = L;
     G.lay_ws.n_keys = 1;
-    Geometry g1 = G.g;
-    g1.n_levels = 1;                    // the scan of a push numbers segments only
+    G.g1 = G.g;
+    G.g1.n_levels = 1;
+    G.g1.no_timeline = true;
     std::vector<uint32_t> vstates;
     for (int32_t i = 0; i < n_props; ++i) {
         const uint32_t ns = ctx->monitors[ctx->props[props[i]].monitor].n_states;
         vstates.insert(vstates.end(), ns, ns);
     }
     G.sgroups = scan_groups(vstates);
-    G.w = plan_workspace(G.lay_ws, g1, max_batch, G.V, (uint32_t)G.sgroups.size(), ctx->sort_variant, ctx->scan_variant);
+    G.w = plan_workspace(G.lay_ws, G.g1, max_batch, G.V, (uint32_t)G.sgroups.size(), ctx->sort_variant, ctx->scan_variant);
     G.seg_keys_off = align256(G.w.total);
     G.ws_bytes = G.seg_keys_off + 8 * max_batch;
     G.state_bytes = group_state_layout(G, L.n_keys, nullptr, nullptr);
@@ -1026,6 +1032,17 @@ int32_t ltl4c_workspace_bytes(ltl4c_ctx* ctx, uint64_t n_events, const int32_t* 
     return LTL4C_OK;
 }
 
+// Where the split map scan keeps its descriptors and records.
+static void set_split(ScanArgs& sa, uint8_t* ws, const WsLayout& w) {
+    sa.desc = ws + w.ms_desc_off;
+    sa.agg = reinterpret_cast<uint32_t*>(ws + w.ms_agg_off);
+    sa.prefix = reinterpret_cast<uint32_t*>(ws + w.ms_prefix_off);
+    sa.trec = reinterpret_cast<uint32_t*>(ws + w.ms_trec_off);
+    sa.chunk_agg = reinterpret_cast<uint32_t*>(ws + w.ms_chunk_off);
+    sa.chunk_pre = sa.chunk_agg + (uint64_t)kMsRec * (w.ms_tiles / kMsSpineThreads + 1);
+    sa.tiles = w.ms_tiles;
+}
+
 // The evaluation pipeline after validation: zero, classify, radix passes,
 // scan, counting per level, finalize.  g.n_levels tree levels; when a chunk
 // table is given the chunk index (a trace id) is the top key.
@@ -1145,19 +1162,7 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
         // writes the verdict timeline on request).  With parent events it runs
         // over the own events and merges the parent events in.
         if (split) {
-            if (!sa.n_dev) {
-                // nothing is excluded: every word counts
-                s = launch(ctx, "scan", [&] { return launch_set_u32(z + w.n_valid_off, (uint32_t)n, st); });
-                if (s) return s;
-                sa.n_dev = z + w.n_valid_off;
-            }
-            sa.desc = ws + w.ms_desc_off;
-            sa.agg = reinterpret_cast<uint32_t*>(ws + w.ms_agg_off);
-            sa.prefix = reinterpret_cast<uint32_t*>(ws + w.ms_prefix_off);
-            sa.trec = reinterpret_cast<uint32_t*>(ws + w.ms_trec_off);
-            sa.chunk_agg = reinterpret_cast<uint32_t*>(ws + w.ms_chunk_off);
-            sa.chunk_pre = sa.chunk_agg + (uint64_t)kMsRec * (w.ms_tiles / kMsSpineThreads + 1);
-            sa.tiles = w.ms_tiles;
+            set_split(sa, ws, w);
         }
         ParentArgs pa{};
         if (g.parent) {
@@ -2141,16 +2146,14 @@ static int32_t group_push_impl(ltl4c_ctx* ctx, int32_t group, const void* d_reco
     auto enqueue = [&]() -> int32_t {
         const hipStream_t st = ctx->stream;
         const ltl4c_layout& L = ctx->layout;
-        const WsLayout& w = G->w;
+        // planned for this push's size: less to clear than for max_batch
+        const WsLayout w = plan_workspace(G->lay_ws, G->g1, n, G->V, (uint32_t)G->sgroups.size(), G->sort_variant, G->scan_variant);
         uint8_t* ws = G->ws;
         uint32_t* z = reinterpret_cast<uint32_t*>(ws);
         {
-            ZeroArgs za{z, nullptr, 0, w.zero_words, 0};
+            ZeroArgs za{z, nullptr, 0, w.zero_words, 0, G->gs.list_cnt, kMaxLevels};
             uint32_t blocks = (uint32_t)std::min<uint64_t>(1024, (w.zero_words + 255) / 256);
             s = launch(ctx, "zero", [&] { return launch_zero(za, blocks ? blocks : 1, st); });
-            if (s) return s;
-            ZeroArgs zl{G->gs.list_cnt, nullptr, 0, kMaxLevels, 0};
-            s = launch(ctx, "zero", [&] { return launch_zero(zl, 1, st); });
             if (s) return s;
         }
         uint64_t* sorted = nullptr;
@@ -2172,14 +2175,19 @@ static int32_t group_push_impl(ltl4c_ctx* ctx, int32_t group, const void* d_reco
             sa.n_props_all = G->V;
             sa.plan = G->vplan;
             sa.inst_verdict = seg_state;
-            sa.inst_stride = G->max_batch;
-            sa.inst_limit = G->max_batch;
+            sa.inst_stride = n;
+            sa.inst_limit = n;
             sa.inst_keys = seg_keys;
             sa.sizes = reinterpret_cast<uint64_t*>(z + w.sizes64_off);
             sa.sizes32 = sizes32;
             sa.err = ctx->err_dev;
             sa.emit_state = 1;
             uint32_t* scan_status = z + w.scan_status_off;
+            const bool split = G->scan_variant == kSplitScanVariant || G->scan_variant == kSplitScanVariant32;
+            if (split) {
+                sa.n_dev = G->g.compact ? z + w.n_valid_off : nullptr;
+                set_split(sa, ws, w);
+            }
             for (size_t gi = 0; gi < G->sgroups.size(); ++gi) {
                 sa.n_props = G->sgroups[gi].cnt;
                 std::memcpy(sa.prop_idx, G->sgroups[gi].idx, sizeof sa.prop_idx);
@@ -2187,7 +2195,11 @@ static int32_t group_push_impl(ltl4c_ctx* ctx, int32_t group, const void* d_reco
                 sa.structure = G->sgroups[gi].structure ? 1u : 0u;
                 sa.status = scan_status + gi * 2ull * kScanRows * w.tiles_scan;
                 sa.ticket = z + w.scan_ticket_off + gi;
-                s = launch(ctx, "scan", [&] { return launch_scan(sa, G->scan_variant, st); });
+                sa.read_desc = gi > 0 ? 1u : 0u;
+                s = launch(ctx, "scan", [&] {
+                    return split ? launch_mapscan(sa, G->scan_variant == kSplitScanVariant32 ? 32 : 16, nullptr, st)
+                                 : launch_scan(sa, G->scan_variant, st);
+                });
                 if (s) return s;
             }
         }
@@ -2196,7 +2208,7 @@ static int32_t group_push_impl(ltl4c_ctx* ctx, int32_t group, const void* d_reco
         ua.n_seg = sizes32;
         ua.seg_key = seg_keys;
         ua.seg_state = seg_state;
-        ua.seg_stride = G->max_batch;
+        ua.seg_stride = n;
         s = launch(ctx, "group_update", [&] { return launch_group_update(ua, n, st); });
         if (s) return s;
         for (int m = (int)L.n_keys - 1; m >= 1; --m) {
