@@ -124,6 +124,7 @@ struct ltl4c_ctx {
     std::vector<ltl4c_property> props;
     std::map<std::vector<int32_t>, Plan*> plans;
     uint32_t* err_dev = nullptr;
+    uint32_t* err_host = nullptr;      // pinned: where ltl4c_wait has the error word copied to
     int sort_variant = kDefaultSortVariant;
     int scan_variant = kDefaultScanVariant;
     uint64_t budget = ~0ull, used = 0;
@@ -507,6 +508,15 @@ int32_t launch(ltl4c_ctx* ctx, const char* name, F&& f) {
     return LTL4C_OK;
 }
 
+// A small host table to device memory inside a launch: a copy of it would wait
+// for the copy engine, some 20 us before the first kernel of a push.
+int32_t put_table(ltl4c_ctx* ctx, uint32_t* dst, const uint32_t* src, uint32_t words) {
+    PutWords pw;
+    pw.n = words;
+    std::memcpy(pw.w, src, 4ull * words);
+    return launch(ctx, "put_words", [&] { return launch_put_words(dst, pw, ctx->stream); });
+}
+
 int32_t drain_profile(ltl4c_ctx* ctx) {
     if (ctx->timed.empty()) return LTL4C_OK;
     HIP_TRY(hipStreamSynchronize(ctx->stream));
@@ -873,6 +883,7 @@ int32_t ltl4c_destroy(ltl4c_ctx* ctx) {
     }
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     (void)hipFree(ctx->err_dev);
+    (void)hipHostFree(ctx->err_host);
     delete ctx;
     return LTL4C_OK;
 }
@@ -1657,6 +1668,12 @@ static int32_t batch_impl(ltl4c_ctx* ctx, const void* d_records, const uint64_t*
         HIP_TRY(hipMalloc(&cap->table_dev, table_bytes));
         HIP_TRY(hipMemcpy(cap->table_dev, h.data(), table_bytes, hipMemcpyHostToDevice));
         table = static_cast<uint32_t*>(cap->table_dev);
+    } else if (table_bytes <= 4ull * kPutWords) {
+        uint32_t h[kPutWords];
+        for (int32_t t = 0; t <= n_traces; ++t) h[t] = (uint32_t)offsets[t];
+        for (int32_t t = 0; t < n_traces; ++t) h[n_traces + 1 + t] = (uint32_t)t;
+        s = put_table(ctx, ctx->batch_chunk_dev, h, (uint32_t)(table_bytes / 4));
+        if (s) return s;
     } else {
         HIP_TRY(hipEventSynchronize(ctx->batch_ev));
         uint32_t* h = ctx->batch_chunk_host;
@@ -1705,9 +1722,11 @@ int32_t ltl4c_eval_batch(ltl4c_ctx* ctx, const void* d_records, const uint64_t* 
 int32_t ltl4c_wait(ltl4c_ctx* ctx) {
     if (!ctx) return fail(LTL4C_EINVAL, "ctx is NULL");
     HIP_TRY(hipSetDevice(ctx->device));
+    // the error word follows the work on the stream into pinned memory: one wait for both
+    if (!ctx->err_host) HIP_TRY(hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault));
+    HIP_TRY(hipMemcpyAsync(ctx->err_host, ctx->err_dev, 4, hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
-    uint32_t err = 0;
-    HIP_TRY(hipMemcpy(&err, ctx->err_dev, 4, hipMemcpyDeviceToHost));
+    const uint32_t err = *ctx->err_host;
     if (err) {
         HIP_TRY(hipMemset(ctx->err_dev, 0, 4));
         if (err & kErrSpin) return fail(LTL4C_EDEVICE, "a look-back wait exceeded its bound");
@@ -2112,9 +2131,13 @@ static int32_t group_push_impl(ltl4c_ctx* ctx, int32_t group, const void* d_reco
     // through the graph's own buffer)
     std::vector<uint32_t> cap_table;
     uint32_t* slot = G->chunk_host + (uint64_t)G->ring_i * kChunkTableWords;
+    uint32_t small[kPutWords];
+    const bool in_launch = !cap && 4ull * n_chunks + 2 <= kPutWords;
     if (cap) {
         cap_table.assign(kChunkTableWords, 0u);
         slot = cap_table.data();
+    } else if (in_launch) {
+        slot = small;
     } else {
         HIP_TRY(hipEventSynchronize(G->ring_ev[G->ring_i]));
     }
@@ -2128,8 +2151,8 @@ static int32_t group_push_impl(ltl4c_ctx* ctx, int32_t group, const void* d_reco
     for (int32_t i = 0; i < n_chunks; ++i) slot[so + i] = streams[i];
     uint64_t words = so + n_chunks;
     if (chunk_ptr) {
-        uint64_t* pp = reinterpret_cast<uint64_t*>(slot + po);
-        for (int32_t i = 0; i < n_chunks; ++i) pp[i] = reinterpret_cast<uint64_t>(chunk_ptr[i]);
+        if (po > words) slot[words] = 0u;
+        std::memcpy(slot + po, chunk_ptr, 8ull * n_chunks);
         words = po + 2ull * n_chunks;
     }
     uint32_t* table = G->chunk_dev;
@@ -2137,6 +2160,9 @@ static int32_t group_push_impl(ltl4c_ctx* ctx, int32_t group, const void* d_reco
         HIP_TRY(hipMalloc(&cap->table_dev, 4 * words));
         HIP_TRY(hipMemcpy(cap->table_dev, slot, 4 * words, hipMemcpyHostToDevice));
         table = static_cast<uint32_t*>(cap->table_dev);
+    } else if (in_launch) {
+        s = put_table(ctx, G->chunk_dev, slot, (uint32_t)words);
+        if (s) return s;
     } else {
         HIP_TRY(hipMemcpyAsync(G->chunk_dev, slot, 4 * words, hipMemcpyHostToDevice, ctx->stream));
         HIP_TRY(hipEventRecord(G->ring_ev[G->ring_i], ctx->stream));

@@ -563,9 +563,13 @@ class StreamGroup:
                                                   C.byref(g)), "ltl4c_group_open_pool")
         self.id = g.value
         t, dev = ctx.torch, f"cuda:{ctx.device}"
-        self.verdict = t.empty(max_streams * len(props), dtype=t.uint8, device=dev)
-        self.counts = t.empty(max_streams * len(props) * 6, dtype=t.int64, device=dev)
-        self.bindings = t.empty(max_streams, dtype=t.int64, device=dev)
+        # counts, bindings and verdicts in one buffer, so that read() copies once
+        cells = max_streams * len(props)
+        self._out = t.empty(56 * cells + 8 * max_streams, dtype=t.uint8, device=dev)
+        self.counts = self._out[:48 * cells].view(t.int64)
+        self.bindings = self._out[48 * cells:48 * cells + 8 * max_streams].view(t.int64)
+        self.verdict = self._out[48 * cells + 8 * max_streams:][:cells]
+        self._host = t.empty(self._out.numel(), dtype=t.uint8, pin_memory=True)
 
     def push(self, records, offsets, streams):
         """Enqueue chunks: records is a device tensor; offsets (len n+1) and
@@ -659,11 +663,14 @@ class StreamGroup:
         _check(self.lib.ltl4c_group_read(self.ctx.h, self.id, C.c_void_p(self.verdict.data_ptr()),
                                          C.c_void_p(self.counts.data_ptr()), C.c_void_p(self.bindings.data_ptr())),
                "ltl4c_group_read")
+        # the copy follows the kernel on the same stream; wait() covers both
+        self._host.copy_(self._out, non_blocking=True)
         self.ctx.wait()
-        P = len(self.props)
-        return (self.verdict.cpu().numpy().reshape(self.max_streams, P),
-                self.counts.cpu().numpy().reshape(self.max_streams, P, 6),
-                self.bindings.cpu().numpy())
+        P, S = len(self.props), self.max_streams
+        host = self._host.numpy().copy()
+        counts = host[:48 * S * P].view(np.int64).reshape(S, P, 6)
+        bindings = host[48 * S * P:48 * S * P + 8 * S].view(np.int64)
+        return host[48 * S * P + 8 * S:][:S * P].reshape(S, P), counts, bindings
 
     def snapshot(self):
         n = C.c_uint64()
