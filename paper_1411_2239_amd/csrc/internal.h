@@ -161,7 +161,7 @@ struct ScanArgs {
     uint32_t* chunk_pre;                 // [chunks][kMsRec] and their exclusive prefixes
     uint32_t spine_chunk;                // tiles per spine chunk
     uint32_t* trec;                      // [kMsThreadRec][tiles * kMsThreads] per thread: its exclusive
-                                         // prefix within the tile (two packed head-count words, map dwords)
+                                         // prefix within the tile (two packed head-count words, maps of 4 bits a state)
     uint32_t tiles;
 };
 // the split map scan: tiles of 256 threads x 16 or 32 words, and their records
@@ -169,7 +169,7 @@ constexpr int kMsThreads = 256;
 constexpr int kMsSpineThreads = 1024;  // the spine block; a spine chunk holds at least this many tiles
 constexpr int kMsTileMin = kMsThreads * 16;   // workspace arrays are sized for the smaller tile
 constexpr int kMsRec = 4 + 16;
-constexpr int kMsThreadRec = 2 + 16;
+constexpr int kMsThreadRec = 2 + 8;
 
 constexpr uint32_t kNever = 0xFFFFFFFFu;     // timeline: the instance never became conclusive
 

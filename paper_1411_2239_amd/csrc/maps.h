@@ -104,6 +104,25 @@ __device__ __forceinline__ BMap<MW> bm_wave_incl_scan(BMap<MW> v) {
     return v;
 }
 
+// the same over the first N lanes alone (N a power of two up to 16: one row)
+template <int N>
+__device__ __forceinline__ uint32_t row_incl_sum(uint32_t v) {
+    if constexpr (N > 1) v += dpp_mov<0x111, 0xF>(0u, v);
+    if constexpr (N > 2) v += dpp_mov<0x112, 0xF>(0u, v);
+    if constexpr (N > 4) v += dpp_mov<0x114, 0xF>(0u, v);
+    if constexpr (N > 8) v += dpp_mov<0x118, 0xF>(0u, v);
+    return v;
+}
+template <int MW, int N>
+__device__ __forceinline__ BMap<MW> bm_row_incl_scan(BMap<MW> v) {
+    static_assert(N <= 16, "one row of lanes");
+    if constexpr (N > 1) v = bm_compose<MW>(v, bm_dpp<MW, 0x111, 0xF>(v));
+    if constexpr (N > 2) v = bm_compose<MW>(v, bm_dpp<MW, 0x112, 0xF>(v));
+    if constexpr (N > 4) v = bm_compose<MW>(v, bm_dpp<MW, 0x114, 0xF>(v));
+    if constexpr (N > 8) v = bm_compose<MW>(v, bm_dpp<MW, 0x118, 0xF>(v));
+    return v;
+}
+
 // the previous lane's value (lane 0: the identity map)
 template <int MW>
 __device__ __forceinline__ BMap<MW> bm_wave_shr1(const BMap<MW>& v) {

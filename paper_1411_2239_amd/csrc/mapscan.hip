@@ -36,6 +36,8 @@ using PeParam = std::conditional_t<PE, ParentArgs, NoParent>;
 // Flags and classes of a thread's run of words: `cnt` valid words (a prefix of
 // the run), head (a new instance), level-m heads (a new level-m node), classes
 // packed 4 bits per word.
+// SYM kernels (classes of at most 3 bits) keep a symbol instead: the class with
+// the head flag in bit 3, so that "restart, then step" is one table entry.
 struct Run {
     uint32_t cnt, m_head, m_lvl[kMaxLevels];
     uint64_t cls[2];
@@ -48,7 +50,7 @@ __device__ __forceinline__ uint32_t run_class(const Run& r, int j) {
 
 __device__ __forceinline__ uint32_t valid_mask(uint32_t cnt) { return cnt >= 32 ? kAll : (1u << cnt) - 1u; }
 
-template <int ITEMS>
+template <int ITEMS, bool SYM>
 __device__ __forceinline__ Run run_from_words(const ScanArgs& a, uint64_t my0, uint32_t n) {
     // Loads are unconditional, so that all of them are in flight together:
     // the word buffers have room for a whole run past the last valid word.
@@ -77,38 +79,40 @@ __device__ __forceinline__ Run run_from_words(const ScanArgs& a, uint64_t my0, u
         const bool first = my0 + j == 0;
         const uint64_t d = prev ^ x;
         prev = x;
-        r.m_head |= (uint32_t)(valid && (first || d >= hlim)) << j;
+        const uint32_t head = (uint32_t)(valid && (first || d >= hlim));
+        r.m_head |= head << j;
 #pragma unroll
         for (int m = 1; m < kMaxLevels; ++m)
             if ((uint32_t)m < a.n_levels) r.m_lvl[m] |= (uint32_t)(valid && (first || d >= llim[m])) << j;
-        const uint64_t cj = (uint64_t)((uint32_t)x & a.class_mask) << (4 * (j & 15));
+        const uint64_t cj = (uint64_t)(((uint32_t)x & a.class_mask) | (SYM ? head << 3 : 0u)) << (4 * (j & 15));
         if (j < 16) r.cls[0] |= cj;
         else r.cls[1] |= cj;
     }
     return r;
 }
 
+template <bool SYM>
 __device__ __forceinline__ uint32_t desc_byte(const Run& r, int j) {
-    uint32_t b = run_class(r, j);
+    uint32_t b = run_class(r, j) & (SYM ? 7u : 15u);
     b |= ((r.m_head >> j) & 1u) << 4;
 #pragma unroll
     for (int m = 1; m < kMaxLevels; ++m) b |= ((r.m_lvl[m] >> j) & 1u) << (4 + m);
     return b;
 }
 
-template <int ITEMS>
+template <int ITEMS, bool SYM>
 __device__ __forceinline__ void store_desc(const ScanArgs& a, uint64_t my0, const Run& r) {
     if (r.cnt == ITEMS) {
         uint32_t d[ITEMS / 4];
 #pragma unroll
         for (int i = 0; i < ITEMS / 4; ++i) d[i] = 0;
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) d[j >> 2] |= desc_byte(r, j) << (8 * (j & 3));
+        for (int j = 0; j < ITEMS; ++j) d[j >> 2] |= desc_byte<SYM>(r, j) << (8 * (j & 3));
         uint4* q = reinterpret_cast<uint4*>(a.desc + my0);
 #pragma unroll
         for (int i = 0; i < ITEMS / 16; ++i) q[i] = make_uint4(d[4 * i], d[4 * i + 1], d[4 * i + 2], d[4 * i + 3]);
     } else {
-        for (uint32_t j = 0; j < r.cnt; ++j) a.desc[my0 + j] = (uint8_t)desc_byte(r, (int)j);
+        for (uint32_t j = 0; j < r.cnt; ++j) a.desc[my0 + j] = (uint8_t)desc_byte<SYM>(r, (int)j);
     }
 }
 
@@ -127,7 +131,7 @@ __device__ __forceinline__ uint32_t transpose4x4(uint32_t y) {   // bit 4k + f -
     return y ^ t ^ (t << 6);
 }
 
-template <int ITEMS>
+template <int ITEMS, bool SYM>
 __device__ __forceinline__ Run run_from_desc(const ScanArgs& a, uint64_t my0, uint32_t n) {
     // (the descriptor buffer has room for a whole run past the last word)
     Run r{};
@@ -148,7 +152,7 @@ __device__ __forceinline__ Run run_from_desc(const ScanArgs& a, uint64_t my0, ui
         uint64_t c = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            c |= (uint64_t)pack_nibbles(d[k] & 0x0F0F0F0Fu) << (16 * k);
+            c |= (uint64_t)pack_nibbles(SYM ? (d[k] & 0x07070707u) | ((d[k] >> 1) & 0x08080808u) : d[k] & 0x0F0F0F0Fu) << (16 * k);
             const uint32_t f = transpose4x4(pack_nibbles((d[k] >> 4) & 0x0F0F0F0Fu));
             const int at = 16 * i + 4 * k;
             r.m_head |= (f & 15u) << at;
@@ -185,6 +189,55 @@ __device__ __forceinline__ void run_maps(const Run& r, uint32_t P, const uint32_
     // (four 16-state maps keep the one path: the second copy costs them registers)
     if (PMAX * MW <= 8 && r.cnt == ITEMS) run_maps_t<PMAX, MW, ITEMS, true>(r, P, s_cm, start_q, f);
     else run_maps_t<PMAX, MW, ITEMS, false>(r, P, s_cm, start_q, f);
+}
+
+// SYM: the map of every symbol (head flag << 3 | class: a head is the constant
+// map of q0's successor), and of every pair of symbols, first one in the low
+// nibble; one pair per thread of the block.
+template <int MW>
+__device__ __forceinline__ BMap<MW> sym_map(const uint32_t (*cm)[MW], uint32_t q0, uint32_t sym) {
+    const BMap<MW> c = bm_load<MW>(cm[sym & 7u]);
+    return (sym & 8u) ? bm_const<MW>(bm_at<MW>(c, q0)) : c;
+}
+template <int PMAX, int MW>
+__device__ __forceinline__ void build_pairs(uint32_t P, const uint32_t (*s_cm)[16][MW], const uint32_t* s_q0,
+                                            uint32_t (*s_pair)[256][MW]) {
+    static_assert(kMsThreads == 256, "one pair per thread");
+    const uint32_t i = threadIdx.x;
+#pragma unroll
+    for (int p = 0; p < PMAX; ++p) {
+        if (p > 0 && p >= (int)P) continue;
+        const BMap<MW> m = bm_compose<MW>(sym_map<MW>(s_cm[p], s_q0[p], i >> 4), sym_map<MW>(s_cm[p], s_q0[p], i & 15u));
+#pragma unroll
+        for (int k = 0; k < MW; ++k) s_pair[p][i][k] = m.d[k];
+    }
+}
+// A full run's maps by pairs: half the compositions and half the table reads of
+// run_maps, and no selects.  The reduce of many or large maps is bound by its
+// vector instructions: 592M events, launches of four 16-state, four 16-state
+// and eight 8-state maps 3400 + 2906 + 1280 us by single words, 2240 + 1723 +
+// 740 us by pairs (with maps of 4 bits per state in the thread records, and the
+// wave totals scanned over their few lanes only).  One or two 8-state maps are
+// bound by memory and keep the single words (10M words 22.6 us, 4.4 TB/s).
+template <int PMAX, int MW, int ITEMS>
+__device__ __forceinline__ void run_maps_pairs(const Run& r, uint32_t P, const uint32_t (*s_pair)[256][MW], BMap<MW>* f) {
+#pragma unroll
+    for (int p = 0; p < PMAX; ++p) {
+        f[p] = bm_identity<MW>();
+        if (p > 0 && p >= (int)P) continue;
+#pragma unroll
+        for (int k = 0; k < ITEMS / 2; ++k) {
+            const BMap<MW> m = bm_load<MW>(s_pair[p][(uint32_t)(r.cls[k >> 3] >> (8 * (k & 7))) & 255u]);
+            f[p] = k ? bm_compose<MW>(m, f[p]) : m;
+        }
+    }
+}
+
+// Maps in the thread records: 4 bits per state.
+template <int MW>
+__device__ __forceinline__ void store_map4(uint32_t* row0, uint64_t row, const BMap<MW>& m) {
+#pragma unroll
+    for (int k = 0; k < MW / 2; ++k) row0[k * row] = pack_nibbles(m.d[2 * k]) | (pack_nibbles(m.d[2 * k + 1]) << 16);
 }
 
 // The bounds of a run's own events, and the events whose gap to the event
@@ -318,7 +371,7 @@ __device__ __forceinline__ void block_scan(uint32_t P, const BMap<MW>* f, const 
         for (int p = 0; p < PMAX; ++p) {
             if (p >= (int)P) continue;
             BMap<MW> v = lane < WAVES ? bm_load<MW>(s_wm[p][lane]) : bm_identity<MW>();
-            v = bm_wave_incl_scan<MW>(v);
+            v = bm_row_incl_scan<MW, WAVES>(v);
             const BMap<MW> ex = bm_wave_shr1<MW>(v);
             if (lane < WAVES) {
 #pragma unroll
@@ -331,7 +384,7 @@ __device__ __forceinline__ void block_scan(uint32_t P, const BMap<MW>* f, const 
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
             const uint32_t c0 = lane < WAVES ? s_wc[k][lane] : 0u;
-            const uint32_t x = wave_incl_sum(c0);
+            const uint32_t x = row_incl_sum<WAVES>(c0);
             if (lane < WAVES) s_wc[k][lane] = x - c0;
             if (lane == WAVES - 1) s_wc[k][WAVES] = x;
         }
@@ -364,9 +417,10 @@ __device__ __forceinline__ void block_scan(uint32_t P, const BMap<MW>* f, const 
 
 }  // namespace
 
-template <int PMAX, int MW, int ITEMS, bool PE>
+template <int PMAX, int MW, int ITEMS, bool PE, bool SYM>
 __global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a, PeParam<PE> q) {
     constexpr uint32_t TILE = kMsThreads * ITEMS;
+    __shared__ uint32_t s_pair[SYM ? PMAX : 1][SYM ? 256 : 1][MW];
     __shared__ uint32_t s_cm[PMAX][16][MW];
     __shared__ uint32_t s_q0[PMAX];
     __shared__ uint32_t s_wm[PMAX][kMsThreads / 64 + 1][MW];
@@ -375,11 +429,15 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a, PeParam<PE
     const uint64_t base = (uint64_t)blockIdx.x * TILE;
     if (base >= n) return;                       // the whole block: no word of this tile
     const uint64_t my0 = base + (uint64_t)threadIdx.x * ITEMS;
-    Run r = a.read_desc ? run_from_desc<ITEMS>(a, my0, n) : run_from_words<ITEMS>(a, my0, n);
+    Run r = a.read_desc ? run_from_desc<ITEMS, SYM>(a, my0, n) : run_from_words<ITEMS, SYM>(a, my0, n);
     const TableRegs tr = read_tables<PMAX, MW>(a);
     store_tables<PMAX, MW>(a, tr, s_cm, s_q0, nullptr);
-    if (!a.read_desc && a.desc && r.cnt) store_desc<ITEMS>(a, my0, r);
+    if (!a.read_desc && a.desc && r.cnt) store_desc<ITEMS, SYM>(a, my0, r);
     __syncthreads();
+    if constexpr (SYM) {
+        build_pairs<PMAX, MW>(a.n_props, s_cm, s_q0, s_pair);
+        __syncthreads();
+    }
     BMap<MW> f[PMAX], excl[PMAX], tot[PMAX];
     if constexpr (PE) {
         const Bounds bd = load_bounds(q, my0, r);
@@ -409,6 +467,19 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a, PeParam<PE
                 }
             }
         }
+    } else if constexpr (SYM) {
+        if (r.cnt == ITEMS) {
+            run_maps_pairs<PMAX, MW, ITEMS>(r, a.n_props, s_pair, f);
+        } else {
+#pragma unroll
+            for (int p = 0; p < PMAX; ++p) {
+                f[p] = bm_identity<MW>();
+                if (p > 0 && p >= (int)a.n_props) continue;
+#pragma unroll 1
+                for (uint32_t j = 0; j < r.cnt; ++j)
+                    f[p] = bm_compose<MW>(sym_map<MW>(s_cm[p], s_q0[p], run_class(r, (int)j)), f[p]);
+            }
+        }
     } else {
         run_maps<PMAX, MW, ITEMS>(r, a.n_props, s_cm, s_q0, f);
     }
@@ -421,12 +492,10 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a, PeParam<PE
     // (rows of consecutive threads: coalesced)
     const uint64_t row = (uint64_t)a.tiles * kMsThreads, at = (uint64_t)blockIdx.x * kMsThreads + threadIdx.x;
     a.trec[at] = cexcl[0] | (cexcl[1] << 16);
-    a.trec[row + at] = cexcl[2] | (cexcl[3] << 16);
+    if (a.n_levels > 2) a.trec[row + at] = cexcl[2] | (cexcl[3] << 16);
 #pragma unroll
     for (int p = 0; p < PMAX; ++p)
-        if (p < (int)a.n_props)
-#pragma unroll
-            for (int k = 0; k < MW; ++k) a.trec[(2 + MW * p + k) * row + at] = excl[p].d[k];
+        if (p < (int)a.n_props) store_map4<MW>(a.trec + (2 + MW / 2 * p) * row + at, row, excl[p]);
     if (threadIdx.x < kMsRec) {
         const uint32_t k = threadIdx.x;
         uint32_t v = 0;
@@ -567,8 +636,9 @@ __global__ __launch_bounds__(kSpineThreads) void k_ms_spine(ScanArgs a) {
 
 // TL: the instantiation that also walks the verdict timeline (its registers
 // stay out of the plain sweep's occupancy)
-template <int PMAX, int MW, int ITEMS, bool TL, bool PE>
+template <int PMAX, int MW, int ITEMS, bool TL, bool PE, bool SYM>
 __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> q) {
+    __shared__ uint8_t s_next[SYM ? PMAX : 1][SYM ? 256 : 1];    // successor of state (low nibble) by symbol (high)
     constexpr uint32_t TILE = kMsThreads * ITEMS;
     constexpr bool kParents = PMAX <= 4;         // LDS room to stage parent ids
     constexpr uint32_t kIvStride = TILE + 1;
@@ -591,33 +661,54 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
     // this thread's prefix within the tile (reduce), the tile's (spine), the
     // descriptors and the one after them
     const uint64_t row = (uint64_t)a.tiles * kMsThreads, at = (uint64_t)blockIdx.x * kMsThreads + tid;
-    const uint32_t c01 = a.trec[at], c23 = a.trec[row + at];
-    BMap<MW> tex[PMAX];
+    const uint32_t c01 = a.trec[at], c23 = a.n_levels > 2 ? a.trec[row + at] : 0u;
+    uint32_t tex[PMAX][MW / 2];
 #pragma unroll
     for (int p = 0; p < PMAX; ++p)
 #pragma unroll
-        for (int k = 0; k < MW; ++k) tex[p].d[k] = a.trec[(2 + MW * p + k) * row + at];
+        for (int k = 0; k < MW / 2; ++k) tex[p][k] = a.trec[(2 + MW / 2 * p + k) * row + at];
+    // Few instances end in the tile (about as many as begin): their states are
+    // found one by one afterwards, each from the last head of its thread's run,
+    // instead of stepping every word of every thread.  592M events of 16
+    // properties, some 256 words per instance: down sweeps of 893 + 884 + 1683 us
+    // stepping every word, 616 + 607 + 837 us so.
+    constexpr bool kList = !TL && !PE;
+    constexpr uint32_t kSparse = 256;
+    __shared__ uint16_t s_end[kList ? kSparse + 1 : 1];
+    __shared__ uint32_t s_hd[kList ? kMsThreads : 1], s_cur[kList ? kMsThreads : 1];
+    __shared__ uint64_t s_cls[kList ? ITEMS / 16 : 1][kList ? kMsThreads : 1];
+    const bool sparse = kList && a.agg[(uint64_t)blockIdx.x * kMsRec] < kSparse;
     const uint32_t* pre = a.prefix + (uint64_t)blockIdx.x * kMsRec;
-    uint32_t tcnt[4], pmap[PMAX][MW];
+    // (state 0's image stands for every state: the map before a tile is
+    // constant, as its first instance restarted from q0)
+    uint32_t tcnt[4], pmap[PMAX];
 #pragma unroll
     for (int k = 0; k < 4; ++k) tcnt[k] = pre[k];
 #pragma unroll
-    for (int p = 0; p < PMAX; ++p)
-#pragma unroll
-        for (int k = 0; k < MW; ++k) pmap[p][k] = pre[4 + MW * p + k];
+    for (int p = 0; p < PMAX; ++p) pmap[p] = pre[4 + MW * p];
     const uint32_t next_desc = a.desc[(my0 < n ? my0 : 0) + ITEMS];
-    const Run r = run_from_desc<ITEMS>(a, my0, n);
+    const Run r = run_from_desc<ITEMS, SYM>(a, my0, n);
     const TableRegs tr = read_tables<PMAX, MW>(a);
     // an instance ends where the next word is absent or a head
     const bool next_head = my0 + ITEMS < n ? ((next_desc >> 4) & 1u) != 0 : true;
     store_tables<PMAX, MW>(a, tr, s_cm, s_q0, s_lab);
     __syncthreads();
+    if constexpr (SYM) {
+#pragma unroll
+        for (int p = 0; p < PMAX; ++p)
+            if (p < (int)P) s_next[p][tid] = (uint8_t)bm_at<MW>(sym_map<MW>(s_cm[p], s_q0[p], (uint32_t)tid >> 4), (uint32_t)tid & (4u * MW - 1u));
+        __syncthreads();
+    }
     uint32_t cexcl[4] = {c01 & 0xFFFFu, c01 >> 16, c23 & 0xFFFFu, c23 >> 16};
     uint32_t cur[PMAX];
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
         cur[p] = 0;
-        if (p < (int)P) cur[p] = bm_at<MW>(bm_compose<MW>(tex[p], bm_load<MW>(pmap[p])), 0);
+        // (both halves shifted before the choice, kept apart: no indexed register array)
+        const uint32_t s0 = pmap[p] & 15u;
+        uint32_t t0 = tex[p][0] >> (4u * (s0 & 7u)), t1 = tex[p][MW / 2 - 1] >> (4u * (s0 & 7u));
+        asm("" : "+v"(t0), "+v"(t1));
+        if (p < (int)P) cur[p] = (MW > 2 && s0 >= 8u ? t1 : t0) & 15u;
     }
     const bool timeline = TL && (a.inst_conc || a.event_pack);
     uint32_t cur0[PMAX];
@@ -633,6 +724,15 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
     const uint32_t lpar = L >= 4 ? 3u : L == 3 ? 2u : 1u;
     const uint32_t par_tile = tcnt[lpar] - 1u, par_local = cexcl[lpar];
     uint32_t my_lo = 0xFFFFFFFFu, my_hi = 0u, err = 0;
+    if (sparse) {
+        uint32_t packed = 0;
+#pragma unroll
+        for (int p = 0; p < PMAX; ++p) packed |= cur[p] << (4 * p);
+        s_cur[tid] = packed;
+#pragma unroll
+        for (int h = 0; h < ITEMS / 16; ++h) s_cls[kList ? h : 0][kList ? tid : 0] = r.cls[h];
+        s_hd[tid] = r.m_head;
+    }
     // First every word's state, without branches (the class maps' LDS reads
     // do not wait on the instance bookkeeping): 4 bits per word and property.
     uint64_t st[PMAX][ITEMS / 16];
@@ -675,15 +775,16 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
             }
         }
     }
+    if (!PE && !sparse)
 #pragma clang loop unroll(full)
     for (int j = 0; j < ITEMS; ++j) {
-        if (PE) break;
         const uint32_t c = run_class(r, j);
         const bool hd = (r.m_head >> j) & 1u;
 #pragma clang loop unroll(full)
         for (int p = 0; p < PMAX; ++p) {    // (a launch has at least one property)
             if (p > 0 && p >= (int)P) continue;
-            cur[p] = bm_at<MW>(bm_load<MW>(s_cm[p][c]), hd ? s_q0[p] : cur[p]);
+            if constexpr (SYM) cur[p] = s_next[p][(c << 4) | cur[p]];
+            else cur[p] = bm_at<MW>(bm_load<MW>(s_cm[p][c]), hd ? s_q0[p] : cur[p]);
             st[p][j >> 4] |= (uint64_t)cur[p] << (4 * (j & 15));
         }
     }
@@ -695,6 +796,8 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
         const uint64_t id = (uint64_t)id_base + slot - 1u;
         if (id < a.inst_limit) {
             const uint32_t sh = 4u * (j & 15u);
+            if (sparse) s_end[slot] = (uint16_t)(tid * ITEMS + j);
+            else
 #pragma clang loop unroll(full)
             for (int p = 0; p < PMAX; ++p) {
                 if (p > 0 && p >= (int)P) continue;
@@ -854,9 +957,37 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
     }
     if (lo < hi) {
         const uint32_t cnt_iv = hi - lo, slot0 = lo + 1u - id_base;
-        for (uint32_t p = 0; p < P; ++p)
-            for (uint32_t i = tid; i < cnt_iv; i += kMsThreads)
-                a.inst_verdict[a.prop_idx[p] * a.inst_stride + lo + i] = s_iv[p * kIvStride + slot0 + i];
+        if (sparse) {
+            for (uint32_t i = tid; i < cnt_iv; i += kMsThreads) {
+                const uint32_t pos = s_end[slot0 + i], t = pos / ITEMS, j = pos % ITEMS;
+                const uint32_t heads = s_hd[t] & (j == 31u ? kAll : (2u << j) - 1u);
+                const uint32_t from = heads ? 31u - (uint32_t)__clz(heads) : 0u;
+                uint32_t q[PMAX];
+#pragma unroll
+                for (int p = 0; p < PMAX; ++p) q[p] = heads ? (p < (int)P ? s_q0[p] : 0u) : (s_cur[t] >> (4 * p)) & 15u;
+                uint64_t sym = s_cls[from >> 4][t] >> (4 * (from & 15u));
+                for (uint32_t k = from; k <= j; ++k, sym >>= 4) {
+                    if (ITEMS > 16 && k == 16u) sym = s_cls[ITEMS / 16 - 1][t];
+                    const uint32_t c = (uint32_t)sym & 15u;
+#pragma clang loop unroll(full)
+                    for (int p = 0; p < PMAX; ++p) {
+                        if (p > 0 && p >= (int)P) continue;
+                        if constexpr (SYM) q[p] = s_next[p][(c << 4) | q[p]];
+                        else q[p] = bm_at<MW>(bm_load<MW>(s_cm[p][c]), q[p]);
+                    }
+                }
+#pragma clang loop unroll(full)
+                for (int p = 0; p < PMAX; ++p) {
+                    if (p > 0 && p >= (int)P) continue;
+                    a.inst_verdict[a.prop_idx[p] * a.inst_stride + lo + i] =
+                        (uint8_t)(a.emit_state ? q[p] : (s_lab[p][q[p] >> 3] >> (4 * (q[p] & 7u))) & 15u);
+                }
+            }
+        } else {
+            for (uint32_t p = 0; p < P; ++p)
+                for (uint32_t i = tid; i < cnt_iv; i += kMsThreads)
+                    a.inst_verdict[a.prop_idx[p] * a.inst_stride + lo + i] = s_iv[p * kIvStride + slot0 + i];
+        }
         if (structure && a.inst_parent && L >= 2)
             for (uint32_t i = tid; i < cnt_iv; i += kMsThreads) a.inst_parent[lo + i] = par_tile + s_par[slot0 + i];
         // the keys in one stream as well: 10M events with 2.9M instances and
@@ -925,13 +1056,13 @@ hipError_t launch_event_unpack(const ScanArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int PMAX, int MW, int ITEMS, bool PE>
+template <int PMAX, int MW, int ITEMS, bool PE, bool SYM>
 static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) {
     const uint32_t tiles = (uint32_t)((a.n + kMsThreads * ITEMS - 1) / (kMsThreads * ITEMS));
     const dim3 grid(tiles ? tiles : 1);
     ScanArgs r = a;
     r.tiles = tiles;
-    hipLaunchKernelGGL((k_ms_reduce<PMAX, MW, ITEMS, PE>), grid, dim3(kMsThreads), 0, s, r, q);
+    hipLaunchKernelGGL((k_ms_reduce<PMAX, MW, ITEMS, PE, SYM>), grid, dim3(kMsThreads), 0, s, r, q);
     // one spine block takes kSpineThreads x chunk records per pass; beyond two
     // passes the chunks are spread over blocks
     constexpr uint32_t kPass = (uint32_t)kSpineThreads * spine_chunk_items<4 + PMAX * MW>();
@@ -949,24 +1080,35 @@ static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) 
     const uint32_t lds = a.structure && a.inst_keys ? 2u * (kMsThreads * ITEMS + 1) : 0u;
     if constexpr (!PE) {
         if (a.inst_conc || a.event_pack) {
-            hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, true, false>), grid, dim3(kMsThreads), lds, s, d, q);
+            hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, true, false, SYM>), grid, dim3(kMsThreads), lds, s, d, q);
             return;
         }
     }
-    hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, false, PE>), grid, dim3(kMsThreads), lds, s, d, q);
+    hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, false, PE, SYM>), grid, dim3(kMsThreads), lds, s, d, q);
+}
+
+template <int PMAX, int MW, int ITEMS, bool PE>
+static void launch_ms_s(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) {
+    if constexpr (!PE && (PMAX >= 4 || MW == 4)) {
+        if (a.class_mask <= 7u) {
+            launch_ms_t<PMAX, MW, ITEMS, PE, true>(a, q, s);
+            return;
+        }
+    }
+    launch_ms_t<PMAX, MW, ITEMS, PE, false>(a, q, s);
 }
 
 template <int ITEMS, bool PE>
 static void launch_ms_items(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) {
     if (a.max_states <= 8) {
-        if (a.n_props <= 1) launch_ms_t<1, 2, ITEMS, PE>(a, q, s);
-        else if (a.n_props <= 2) launch_ms_t<2, 2, ITEMS, PE>(a, q, s);
-        else if (a.n_props <= 4) launch_ms_t<4, 2, ITEMS, PE>(a, q, s);
-        else launch_ms_t<8, 2, ITEMS, PE>(a, q, s);
+        if (a.n_props <= 1) launch_ms_s<1, 2, ITEMS, PE>(a, q, s);
+        else if (a.n_props <= 2) launch_ms_s<2, 2, ITEMS, PE>(a, q, s);
+        else if (a.n_props <= 4) launch_ms_s<4, 2, ITEMS, PE>(a, q, s);
+        else launch_ms_s<8, 2, ITEMS, PE>(a, q, s);
     } else {
-        if (a.n_props <= 1) launch_ms_t<1, 4, ITEMS, PE>(a, q, s);
-        else if (a.n_props <= 2) launch_ms_t<2, 4, ITEMS, PE>(a, q, s);
-        else launch_ms_t<4, 4, ITEMS, PE>(a, q, s);
+        if (a.n_props <= 1) launch_ms_s<1, 4, ITEMS, PE>(a, q, s);
+        else if (a.n_props <= 2) launch_ms_s<2, 4, ITEMS, PE>(a, q, s);
+        else launch_ms_s<4, 4, ITEMS, PE>(a, q, s);
     }
 }
 
