@@ -156,7 +156,8 @@ struct ScanArgs {
     uint8_t* desc;                       // [n] per word: class | head << 4 | level-m heads << (4 + m)
     uint32_t read_desc;                  // 1: read the descriptors instead of the words
     uint32_t* agg;                       // [tiles][kMsRec] tile aggregates: 4 head counts, map dwords
-    uint32_t* prefix;                    // [tiles][kMsRec] exclusive prefixes of the aggregates
+    uint32_t* prefix;                    // [tiles][kMsRec] exclusive prefixes of the aggregates (null in a down sweep
+                                         // that composes its own)
     uint32_t* chunk_agg;                 // [chunks][kMsRec] spine of many tiles: chunk compositions
     uint32_t* chunk_pre;                 // [chunks][kMsRec] and their exclusive prefixes
     uint32_t spine_chunk;                // tiles per spine chunk

@@ -28,6 +28,14 @@ namespace {
 
 constexpr uint32_t kAll = 0xFFFFFFFFu;
 
+// Words of a tile record in memory: four counts and the maps, in whole 16-byte
+// parts (the arrays are sized for kMsRec).
+template <int PMAX, int MW>
+constexpr uint32_t ms_rec() {
+    static_assert(4 + PMAX * MW <= kMsRec, "record fits the arrays");
+    return (4 + PMAX * MW + 3) / 4 * 4;
+}
+
 // PE kernels merge parent events in (parent.hip prepares what they read).
 struct NoParent {};
 template <bool PE>
@@ -496,7 +504,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a, PeParam<PE
 #pragma unroll
     for (int p = 0; p < PMAX; ++p)
         if (p < (int)a.n_props) store_map4<MW>(a.trec + (2 + MW / 2 * p) * row + at, row, excl[p]);
-    if (threadIdx.x < kMsRec) {
+    if (threadIdx.x < ms_rec<PMAX, MW>()) {
         const uint32_t k = threadIdx.x;
         uint32_t v = 0;
         if (k < 4) {
@@ -509,7 +517,7 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_reduce(ScanArgs a, PeParam<PE
                 for (int e = 0; e < MW; ++e)
                     if ((uint32_t)q == p && (uint32_t)e == d) v = tot[q].d[e];
         }
-        a.agg[(uint64_t)blockIdx.x * kMsRec + k] = v;
+        a.agg[(uint64_t)blockIdx.x * ms_rec<PMAX, MW>() + k] = v;
     }
 }
 
@@ -532,8 +540,7 @@ __global__ __launch_bounds__(kSpineThreads) void k_ms_spine(ScanArgs a) {
     constexpr uint32_t TILE = kMsThreads * ITEMS;
     constexpr int NW = 4 + PMAX * MW;            // record words in use
     constexpr int kSpineChunk = spine_chunk_items<NW>();    // records held in registers
-    constexpr int NQ = (NW + 3) / 4;             // 16-byte parts of a record (records are 80 bytes)
-    static_assert(kMsRec % 4 == 0 && NQ * 4 <= kMsRec, "records load as whole 16-byte parts");
+    constexpr int NQ = (NW + 3) / 4;             // 16-byte parts of a record
     __shared__ uint32_t s_wm[PMAX][kSpineThreads / 64 + 1][MW];
     __shared__ uint32_t s_wc[4][kSpineThreads / 64 + 1];
     __shared__ uint32_t s_carry[NW];
@@ -555,7 +562,7 @@ __global__ __launch_bounds__(kSpineThreads) void k_ms_spine(ScanArgs a) {
     }
     if (threadIdx.x < NW) {
         uint32_t v = threadIdx.x < 4 ? 0u : bm_identity<MW>().d[(threadIdx.x - 4) % MW];
-        if (MODE == 3) v = a.chunk_pre[(uint64_t)blockIdx.x * kMsRec + threadIdx.x];
+        if (MODE == 3) v = a.chunk_pre[(uint64_t)blockIdx.x * ms_rec<PMAX, MW>() + threadIdx.x];
         s_carry[threadIdx.x] = v;
     }
     __syncthreads();
@@ -567,7 +574,7 @@ __global__ __launch_bounds__(kSpineThreads) void k_ms_spine(ScanArgs a) {
 #pragma unroll
         for (int i = 0; i < kSpineChunk; ++i) {
             const uint32_t t = min(t0 + (uint32_t)i, r1 - 1u);
-            const uint4* src = reinterpret_cast<const uint4*>(in + (uint64_t)t * kMsRec);
+            const uint4* src = reinterpret_cast<const uint4*>(in + (uint64_t)t * ms_rec<PMAX, MW>());
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 const uint4 v = src[q];
@@ -602,7 +609,7 @@ __global__ __launch_bounds__(kSpineThreads) void k_ms_spine(ScanArgs a) {
 #pragma unroll
             for (int i = 0; i < kSpineChunk; ++i) {
                 if ((uint32_t)i >= cnt) continue;
-                uint32_t* o = out + (uint64_t)(t0 + i) * kMsRec;
+                uint32_t* o = out + (uint64_t)(t0 + i) * ms_rec<PMAX, MW>();
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     o[k] = cc[k];
@@ -631,7 +638,62 @@ __global__ __launch_bounds__(kSpineThreads) void k_ms_spine(ScanArgs a) {
         __syncthreads();
     }
     // the chunk's record: its composition (the carry started at the identity)
-    if (MODE == 1 && threadIdx.x < NW) a.chunk_agg[(uint64_t)blockIdx.x * kMsRec + threadIdx.x] = s_carry[threadIdx.x];
+    if (MODE == 1 && threadIdx.x < NW) a.chunk_agg[(uint64_t)blockIdx.x * ms_rec<PMAX, MW>() + threadIdx.x] = s_carry[threadIdx.x];
+}
+
+// Before a tile: its state per property (the tile maps before it composed, at
+// state 0: the first of them begins with a head, so the composition is
+// constant) and its head counts, from the records of all tiles before it.  Each
+// thread composes a contiguous share, the waves scan theirs in lane order and
+// leave their totals in s_wm / s_wc; the caller adds those up after a barrier.
+template <int PMAX, int MW>
+__device__ __forceinline__ void compose_before(const ScanArgs& a, uint32_t P, uint32_t (*s_wm)[kMsThreads / 64][MW],
+                                               uint32_t (*s_wc)[kMsThreads / 64]) {
+    constexpr int NW = 4 + PMAX * MW, NQ = (NW + 3) / 4, kBatch = spine_chunk_items<NW>();
+    const uint32_t b = blockIdx.x, share = (b + kMsThreads - 1) / kMsThreads;
+    const uint32_t t0 = min(b, threadIdx.x * share), t1 = min(b, t0 + share);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    BMap<MW> f[PMAX];
+    uint32_t c[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int p = 0; p < PMAX; ++p) f[p] = bm_identity<MW>();
+    for (uint32_t t = t0; t < t1; t += kBatch) {
+        uint32_t rec[kBatch][NQ * 4];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {      // unconditional loads of clamped records, all in flight together
+            const uint4* src = reinterpret_cast<const uint4*>(a.agg + (uint64_t)min(t + (uint32_t)i, t1 - 1u) * ms_rec<PMAX, MW>());
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const uint4 v = src[q];
+                rec[i][4 * q] = v.x;
+                rec[i][4 * q + 1] = v.y;
+                rec[i][4 * q + 2] = v.z;
+                rec[i][4 * q + 3] = v.w;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const bool in = t + (uint32_t)i < t1;
+#pragma unroll
+            for (int p = 0; p < PMAX; ++p)
+                if (p < (int)P && in) f[p] = bm_compose<MW>(bm_load<MW>(&rec[i][4 + MW * p]), f[p]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[k] += in ? rec[i][k] : 0u;
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < PMAX; ++p) {
+        if (p >= (int)P) continue;
+        const BMap<MW> v = bm_wave_incl_scan<MW>(f[p]);
+        if (lane == 63)
+#pragma unroll
+            for (int k = 0; k < MW; ++k) s_wm[p][w][k] = v.d[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t x = (uint32_t)k < a.n_levels ? wave_incl_sum(c[k]) : 0u;
+        if (lane == 63) s_wc[k][w] = x;
+    }
 }
 
 // TL: the instantiation that also walks the verdict timeline (its registers
@@ -677,22 +739,39 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
     __shared__ uint16_t s_end[kList ? kSparse + 1 : 1];
     __shared__ uint32_t s_hd[kList ? kMsThreads : 1], s_cur[kList ? kMsThreads : 1];
     __shared__ uint64_t s_cls[kList ? ITEMS / 16 : 1][kList ? kMsThreads : 1];
-    const bool sparse = kList && a.agg[(uint64_t)blockIdx.x * kMsRec] < kSparse;
-    const uint32_t* pre = a.prefix + (uint64_t)blockIdx.x * kMsRec;
-    // (state 0's image stands for every state: the map before a tile is
-    // constant, as its first instance restarted from q0)
-    uint32_t tcnt[4], pmap[PMAX];
+    const bool sparse = kList && a.agg[(uint64_t)blockIdx.x * ms_rec<PMAX, MW>()] < kSparse;
+    // what comes before the tile: from the spine, or composed here
+    __shared__ uint32_t s_wm[PMAX][kMsThreads / 64][MW];
+    __shared__ uint32_t s_wc[4][kMsThreads / 64];
+    uint32_t tcnt[4] = {0, 0, 0, 0}, pmap[PMAX];
+    if (a.prefix) {
+        const uint32_t* pre = a.prefix + (uint64_t)blockIdx.x * ms_rec<PMAX, MW>();
 #pragma unroll
-    for (int k = 0; k < 4; ++k) tcnt[k] = pre[k];
+        for (int k = 0; k < 4; ++k) tcnt[k] = pre[k];
 #pragma unroll
-    for (int p = 0; p < PMAX; ++p) pmap[p] = pre[4 + MW * p];
+        for (int p = 0; p < PMAX; ++p) pmap[p] = pre[4 + MW * p];     // (state 0's image: the map is constant)
+    }
     const uint32_t next_desc = a.desc[(my0 < n ? my0 : 0) + ITEMS];
     const Run r = run_from_desc<ITEMS, SYM>(a, my0, n);
     const TableRegs tr = read_tables<PMAX, MW>(a);
     // an instance ends where the next word is absent or a head
     const bool next_head = my0 + ITEMS < n ? ((next_desc >> 4) & 1u) != 0 : true;
     store_tables<PMAX, MW>(a, tr, s_cm, s_q0, s_lab);
+    if (!a.prefix) compose_before<PMAX, MW>(a, P, s_wm, s_wc);
     __syncthreads();
+    if (!a.prefix) {
+#pragma unroll
+        for (int p = 0; p < PMAX; ++p) {
+            pmap[p] = 0;
+            if (p >= (int)P) continue;
+#pragma unroll
+            for (int i = 0; i < kMsThreads / 64; ++i) pmap[p] = bm_at<MW>(bm_load<MW>(s_wm[p][i]), pmap[p]);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < kMsThreads / 64; ++i) tcnt[k] += s_wc[k][i];
+    }
     if constexpr (SYM) {
 #pragma unroll
         for (int p = 0; p < PMAX; ++p)
@@ -1056,6 +1135,13 @@ hipError_t launch_event_unpack(const ScanArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Up to this many tiles every block of the down sweep composes what comes
+// before it by itself instead of waiting for a spine block, a launch less: 1M
+// words, one property, down sweep 9.0 us and spine 5.0 -> 9.9 us; 10M words 19.3
+// and 11.7 -> 26.6 us.  The records read grow with the square of the tiles, so
+// longer traces keep the spine.
+constexpr uint32_t kOwnTiles = 2560;
+
 template <int PMAX, int MW, int ITEMS, bool PE, bool SYM>
 static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) {
     const uint32_t tiles = (uint32_t)((a.n + kMsThreads * ITEMS - 1) / (kMsThreads * ITEMS));
@@ -1066,7 +1152,9 @@ static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) 
     // one spine block takes kSpineThreads x chunk records per pass; beyond two
     // passes the chunks are spread over blocks
     constexpr uint32_t kPass = (uint32_t)kSpineThreads * spine_chunk_items<4 + PMAX * MW>();
-    if (tiles <= 2 * kPass || !a.chunk_agg || !a.chunk_pre) {
+    if (tiles <= kOwnTiles) {
+        r.prefix = nullptr;
+    } else if (tiles <= 2 * kPass || !a.chunk_agg || !a.chunk_pre) {
         hipLaunchKernelGGL((k_ms_spine<PMAX, MW, ITEMS, 0>), dim3(1), dim3(kSpineThreads), 0, s, r);
     } else {
         r.spine_chunk = kPass;
