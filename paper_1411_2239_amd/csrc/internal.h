@@ -12,6 +12,7 @@ constexpr int kStates = 16;          // monitor states, at most (a map holds one
 constexpr int kRadixBits = 8;
 constexpr int kRadixBitsWide = 9;        // digit of the passes of 512-thread tiles, when it saves a pass
 constexpr int kHistWords = 4096;         // classify's histograms: n_pass << digit bits, at most
+constexpr uint32_t kHistCopies = 4;      // of them in memory
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 16;
 constexpr int kSortTile = kSortThreads * kSortItems;     // 4096 words per tile
@@ -73,7 +74,7 @@ struct ClassifyArgs {
     uint32_t sort_shift;             // lowest sorted bit
     const Plan* plan;
     uint64_t* words;
-    uint32_t* hist;                  // [n_pass][1 << digit_bits]
+    uint32_t* hist;                  // [kHistCopies][n_pass][1 << digit_bits]
     uint32_t* n_valid;               // non-null: count of events kept; excluded events enter no histogram
     uint32_t* err;
     // stream groups: event i belongs to the chunk c with
@@ -105,7 +106,8 @@ struct SortPassArgs {
     uint32_t n;                      // words in `in` (an upper bound when n_valid is set)
     uint32_t shift;                  // lowest bit of this pass's digit
     uint32_t nbits;                  // digit width (<= the kernel's digit bits)
-    const uint32_t* hist;            // this pass's global histogram [buckets]
+    const uint32_t* hist;            // this pass's global histogram [buckets], kHistCopies of them to be summed
+    uint32_t hist_stride;            // from one copy to the next
     uint32_t* status;                // [tiles, then groups of tiles][buckets] look-back words
     uint32_t* ticket;
     const uint32_t* n_valid;         // non-null: words kept by the first pass (device)
@@ -336,7 +338,7 @@ struct RankArgs {
     uint32_t has_key[8];                 // bit t: events of type t carry this level's key
     uint32_t level, key_dw, key_shift, key_mask;
     uint64_t* words;                     // prep: value << 32 | event index
-    uint32_t* hist;                      // prep: [4][256] histograms of the value's bytes
+    uint32_t* hist;                      // prep: [kHistCopies][4][256] histograms of the value's bytes
     const uint64_t* sorted;              // the words after the radix passes over the value
     uint32_t* tile_cnt;                  // [tiles] distinct-value heads per tile
     uint32_t* tile_off;                  // [tiles] heads before each tile

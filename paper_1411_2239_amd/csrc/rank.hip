@@ -36,7 +36,7 @@ __global__ __launch_bounds__(1024) void k_rank_prep(RankArgs a) {
     __syncthreads();
     for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) {
         const uint32_t v = s_hist[i];
-        if (v) atomicAdd(a.hist + i, v);
+        if (v) atomicAdd(a.hist + (blockIdx.x % kHistCopies) * 4u * 256u + i, v);
     }
 }
 

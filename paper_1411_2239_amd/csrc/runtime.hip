@@ -265,7 +265,7 @@ WsLayout plan_workspace(const ltl4c_layout& L, const Geometry& g, uint64_t n, ui
     w.tiles_scan = (uint32_t)((n + sct - 1) / sct);
     // zero block, in 32-bit words
     uint64_t z = 0;
-    w.hist_off = z;        z += (uint64_t)g.n_pass << g.digit_bits;
+    w.hist_off = z;        z += ((uint64_t)kHistCopies * g.n_pass) << g.digit_bits;
     w.n_valid_off = z;     z += 64;
     w.sort_ticket_off = z; z += 64;
     w.scan_ticket_off = z; z += 64;
@@ -377,7 +377,7 @@ ltl4c_layout rank_sized(const ltl4c_layout& L, uint64_t n) {
 // The ranking area at the start of the workspace (the evaluation's own
 // workspace follows it).  Offsets in bytes.
 struct RankRegion {
-    uint64_t zero_off, zero_words;        // histograms [4][256], tickets, look-back status [4][tiles][256]
+    uint64_t zero_off, zero_words;        // histograms [kHistCopies][4][256], tickets, look-back status [4][tiles][256]
     uint64_t hist_w, ticket_w, status_w;  // word offsets inside the zero block
     uint64_t distinct_off;                // [4] distinct values per level
     uint64_t tile_cnt_off, tile_off_off;
@@ -390,7 +390,7 @@ RankRegion rank_region(const ltl4c_layout& L, uint64_t n, int sort_variant) {
     RankRegion r{};
     r.sort_rows = sort_status_rows(sort_variant, n);
     r.hist_w = 0;
-    r.ticket_w = 4 * 256;
+    r.ticket_w = kHistCopies * 4 * 256;
     r.status_w = r.ticket_w + 64;
     r.zero_words = r.status_w + 4ull * r.sort_rows * 256;
     uint64_t off = 0;
@@ -615,6 +615,7 @@ int32_t enqueue_front(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& g, 
         sa.shift = g.cbits + g.ibits + g.digit_bits * p;
         sa.nbits = std::min<uint32_t>(g.digit_bits, g.sort_bits - g.digit_bits * p);
         sa.hist = hist + ((uint64_t)p << g.digit_bits);
+        sa.hist_stride = g.n_pass << g.digit_bits;
         sa.status = sort_status + ((p * w.sort_rows) << g.digit_bits);
         sa.ticket = sort_ticket + p;
         sa.n_valid = ca.n_valid;
@@ -1348,6 +1349,7 @@ static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* 
             sa.shift = 32 + 8 * p;
             sa.nbits = 8;
             sa.hist = z + rr.hist_w + 256 * p;
+            sa.hist_stride = 4 * 256;
             sa.status = z + rr.status_w + p * rr.sort_rows * 256;
             sa.ticket = z + rr.ticket_w + p;
             sa.err = ctx->err_dev;
