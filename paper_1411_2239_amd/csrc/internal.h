@@ -12,7 +12,8 @@ constexpr int kStates = 16;          // monitor states, at most (a map holds one
 constexpr int kRadixBits = 8;
 constexpr int kRadixBitsWide = 9;        // digit of the passes of 512-thread tiles, when it saves a pass
 constexpr int kHistWords = 4096;         // classify's histograms: n_pass << digit bits, at most
-constexpr uint32_t kHistCopies = 4;      // of them in memory
+constexpr uint32_t kHistCopies = 4;      // of them in memory, for traces below kShortTrace events
+constexpr uint64_t kShortTrace = 6000000;
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 16;
 constexpr int kSortTile = kSortThreads * kSortItems;     // 4096 words per tile
@@ -70,11 +71,13 @@ struct ClassifyArgs {
     uint32_t ibits;                  // trace index bits between the class and the key (0: none)
     uint32_t excl_shift;             // bit set in the word of an excluded event
     uint32_t n_pass;                 // radix passes whose histograms are built here
-    uint32_t digit_bits;             // radix digit width (8 or 9)
+    uint32_t digit_bits;             // radix digit width of the kernel (8 or 9): the histograms' stride
+    uint32_t digit_step;             // bits of each digit (at most digit_bits)
     uint32_t sort_shift;             // lowest sorted bit
     const Plan* plan;
     uint64_t* words;
-    uint32_t* hist;                  // [kHistCopies][n_pass][1 << digit_bits]
+    uint32_t* hist;                  // [hist_copies][n_pass][1 << digit_bits]
+    uint32_t hist_copies;
     uint32_t* n_valid;               // non-null: count of events kept; excluded events enter no histogram
     uint32_t* err;
     // stream groups: event i belongs to the chunk c with
@@ -106,8 +109,8 @@ struct SortPassArgs {
     uint32_t n;                      // words in `in` (an upper bound when n_valid is set)
     uint32_t shift;                  // lowest bit of this pass's digit
     uint32_t nbits;                  // digit width (<= the kernel's digit bits)
-    const uint32_t* hist;            // this pass's global histogram [buckets], kHistCopies of them to be summed
-    uint32_t hist_stride;            // from one copy to the next
+    const uint32_t* hist;            // this pass's global histogram [buckets] (kHistCopies of them to be summed)
+    uint32_t hist_stride;            // from one copy to the next; 0: a single copy
     uint32_t* status;                // [tiles, then groups of tiles][buckets] look-back words
     uint32_t* ticket;
     const uint32_t* n_valid;         // non-null: words kept by the first pass (device)
@@ -158,8 +161,7 @@ struct ScanArgs {
     uint8_t* desc;                       // [n] per word: class | head << 4 | level-m heads << (4 + m)
     uint32_t read_desc;                  // 1: read the descriptors instead of the words
     uint32_t* agg;                       // [tiles][kMsRec] tile aggregates: 4 head counts, map dwords
-    uint32_t* prefix;                    // [tiles][kMsRec] exclusive prefixes of the aggregates (null in a down sweep
-                                         // that composes its own)
+    uint32_t* prefix;                    // [tiles][kMsRec] exclusive prefixes of the aggregates
     uint32_t* chunk_agg;                 // [chunks][kMsRec] spine of many tiles: chunk compositions
     uint32_t* chunk_pre;                 // [chunks][kMsRec] and their exclusive prefixes
     uint32_t spine_chunk;                // tiles per spine chunk

@@ -205,7 +205,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         s_cls[i] = a.plan->class_of_type[i];
         s_kp[i] = a.plan->key_present[i];
     }
-    const uint32_t n_hist = a.n_pass << a.digit_bits, dmask = (1u << a.digit_bits) - 1u;
+    const uint32_t n_hist = a.n_pass << a.digit_bits, dmask = (1u << a.digit_step) - 1u;
     for (uint32_t i = threadIdx.x; i < n_hist; i += blockDim.x) s_hist[i] = 0;
     if (threadIdx.x == 0) s_nvalid = s_npar = 0;
     if constexpr (GROUP) {
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         if (ok || !a.n_valid) {
             kept += ok;
             for (uint32_t p = 0; p < a.n_pass; ++p) {
-                const uint32_t bin = (p << a.digit_bits) + ((uint32_t)(word >> (a.sort_shift + a.digit_bits * p)) & dmask);
+                const uint32_t bin = (p << a.digit_bits) + ((uint32_t)(word >> (a.sort_shift + a.digit_step * p)) & dmask);
                 if constexpr (GROUP) {
                     // a wave's records mostly share the chunk, so the digits of
                     // the stream or trace id are all one: 64 lanes adding to
@@ -351,8 +351,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     // The blocks end together and add to the same bins, one after another per
     // bin: kHistCopies copies of the histograms (the radix passes sum them)
     // take that many adds at once.  1M 12-byte records 14.6 -> 13.0 us, 1M
-    // 16-byte records 16.4 -> 15.5 us.
-    uint32_t* hist = a.hist + (blockIdx.x % kHistCopies) * (uint64_t)n_hist;
+    // 16-byte records 16.4 -> 15.5 us; long traces take one copy, as the tiles of
+    // every pass then have nothing to sum (10M users 344 -> 340 us a pass).
+    uint32_t* hist = a.hist + (blockIdx.x % a.hist_copies) * (uint64_t)n_hist;
     for (uint32_t i = threadIdx.x; i < n_hist; i += blockDim.x) {
         const uint32_t v = s_hist[i];
         if (v) atomicAdd(hist + i, v);
@@ -439,9 +440,16 @@ void k_sort_pass(SortPassArgs a) {
     for (int r = 0; r < ITEMS; ++r)
         if ((uint32_t)r * 64 < rem && !(a.drop_excl && (key[r] >> a.excl_shift) != 0)) vm |= 1u << r;
     uint32_t h = 0;
-    if (tid < B)
+    if (tid < B) {
+        h = a.hist[tid];
+        if (a.hist_stride) {                   // (uniform) kHistCopies copies
+            uint32_t more[kHistCopies - 1];
 #pragma unroll
-        for (uint32_t c = 0; c < kHistCopies; ++c) h += a.hist[c * a.hist_stride + tid];
+            for (uint32_t c = 1; c < kHistCopies; ++c) more[c - 1] = a.hist[c * a.hist_stride + tid];
+#pragma unroll
+            for (uint32_t c = 1; c < kHistCopies; ++c) h += more[c - 1];
+        }
+    }
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) dr[r] = (uint32_t)(key[r] >> a.shift) & dmask;
     // rank inside the wave: lanes with the same digit found by one ballot per
@@ -1764,7 +1772,7 @@ hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s) {
     // short traces take fewer blocks: 0.3M records 12.6 us with 512 at most and
     // 10.4 with 128, 1M 20.3 and 16.4 (256), 4M 27.8 and 26.4, but 10M 48.8
     // and 51.9.
-    const uint64_t want = (a.n + 1023) / 1024, cap = a.n < (1u << 19) ? 128 : a.n < 6000000u ? 256 : 512;
+    const uint64_t want = (a.n + 1023) / 1024, cap = a.n < (1u << 19) ? 128 : a.n < kShortTrace ? 256 : 512;
     const uint32_t blocks = (uint32_t)(want < cap ? (want ? want : 1) : cap);
     if (a.record_bytes == 16 && (reinterpret_cast<uintptr_t>(a.records) & 15) == 0 && a.vec_ok) launch_classify_r<4>(a, blocks, s);
     else if (a.record_bytes == 12) launch_classify_r<3>(a, blocks, s);

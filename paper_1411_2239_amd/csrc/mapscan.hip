@@ -698,7 +698,9 @@ __device__ __forceinline__ void compose_before(const ScanArgs& a, uint32_t P, ui
 
 // TL: the instantiation that also walks the verdict timeline (its registers
 // stay out of the plain sweep's occupancy)
-template <int PMAX, int MW, int ITEMS, bool TL, bool PE, bool SYM>
+// OWN: the instantiation whose blocks compose what comes before them (again,
+// its registers cost the others blocks per CU: batch down sweeps 616 -> 668 us).
+template <int PMAX, int MW, int ITEMS, bool TL, bool PE, bool SYM, bool OWN>
 __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> q) {
     __shared__ uint8_t s_next[SYM ? PMAX : 1][SYM ? 256 : 1];    // successor of state (low nibble) by symbol (high)
     constexpr uint32_t TILE = kMsThreads * ITEMS;
@@ -741,10 +743,10 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
     __shared__ uint64_t s_cls[kList ? ITEMS / 16 : 1][kList ? kMsThreads : 1];
     const bool sparse = kList && a.agg[(uint64_t)blockIdx.x * ms_rec<PMAX, MW>()] < kSparse;
     // what comes before the tile: from the spine, or composed here
-    __shared__ uint32_t s_wm[PMAX][kMsThreads / 64][MW];
-    __shared__ uint32_t s_wc[4][kMsThreads / 64];
+    __shared__ uint32_t s_wm[OWN ? PMAX : 1][kMsThreads / 64][MW];
+    __shared__ uint32_t s_wc[OWN ? 4 : 1][kMsThreads / 64];
     uint32_t tcnt[4] = {0, 0, 0, 0}, pmap[PMAX];
-    if (a.prefix) {
+    if constexpr (!OWN) {
         const uint32_t* pre = a.prefix + (uint64_t)blockIdx.x * ms_rec<PMAX, MW>();
 #pragma unroll
         for (int k = 0; k < 4; ++k) tcnt[k] = pre[k];
@@ -757,9 +759,9 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
     // an instance ends where the next word is absent or a head
     const bool next_head = my0 + ITEMS < n ? ((next_desc >> 4) & 1u) != 0 : true;
     store_tables<PMAX, MW>(a, tr, s_cm, s_q0, s_lab);
-    if (!a.prefix) compose_before<PMAX, MW>(a, P, s_wm, s_wc);
+    if constexpr (OWN) compose_before<PMAX, MW>(a, P, s_wm, s_wc);
     __syncthreads();
-    if (!a.prefix) {
+    if constexpr (OWN) {
 #pragma unroll
         for (int p = 0; p < PMAX; ++p) {
             pmap[p] = 0;
@@ -1135,6 +1137,17 @@ hipError_t launch_event_unpack(const ScanArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int PMAX, int MW, int ITEMS, bool TL, bool PE, bool SYM>
+static void launch_down(const ScanArgs& d, const PeParam<PE>& q, bool own, dim3 grid, uint32_t lds, hipStream_t s) {
+    if constexpr (ITEMS == 16) {
+        if (own) {
+            hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, TL, PE, SYM, true>), grid, dim3(kMsThreads), lds, s, d, q);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, TL, PE, SYM, false>), grid, dim3(kMsThreads), lds, s, d, q);
+}
+
 // Up to this many tiles every block of the down sweep composes what comes
 // before it by itself instead of waiting for a spine block, a launch less: 1M
 // words, one property, down sweep 9.0 us and spine 5.0 -> 9.9 us; 10M words 19.3
@@ -1152,8 +1165,8 @@ static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) 
     // one spine block takes kSpineThreads x chunk records per pass; beyond two
     // passes the chunks are spread over blocks
     constexpr uint32_t kPass = (uint32_t)kSpineThreads * spine_chunk_items<4 + PMAX * MW>();
-    if (tiles <= kOwnTiles) {
-        r.prefix = nullptr;
+    const bool own = ITEMS == 16 && tiles <= kOwnTiles;
+    if (own) {
     } else if (tiles <= 2 * kPass || !a.chunk_agg || !a.chunk_pre) {
         hipLaunchKernelGGL((k_ms_spine<PMAX, MW, ITEMS, 0>), dim3(1), dim3(kSpineThreads), 0, s, r);
     } else {
@@ -1168,11 +1181,11 @@ static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) 
     const uint32_t lds = a.structure && a.inst_keys ? 2u * (kMsThreads * ITEMS + 1) : 0u;
     if constexpr (!PE) {
         if (a.inst_conc || a.event_pack) {
-            hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, true, false, SYM>), grid, dim3(kMsThreads), lds, s, d, q);
+            launch_down<PMAX, MW, ITEMS, true, false, SYM>(d, q, own, grid, lds, s);
             return;
         }
     }
-    hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, false, PE, SYM>), grid, dim3(kMsThreads), lds, s, d, q);
+    launch_down<PMAX, MW, ITEMS, false, PE, SYM>(d, q, own, grid, lds, s);
 }
 
 template <int PMAX, int MW, int ITEMS, bool PE>
