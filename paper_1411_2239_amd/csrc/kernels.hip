@@ -1128,7 +1128,24 @@ __device__ __forceinline__ void finalize_root(const FinalizeArgs& a) {
     for (int b = 0; b < 6; ++b) a.root_counts_out[p * 6 + b] = v[b];
 }
 
-__global__ void k_finalize(FinalizeArgs a) { finalize_root(a); }
+// The same from several copies of the bins: one thread sums each bin.
+__global__ __launch_bounds__(128) void k_finalize(FinalizeArgs a) {
+    __shared__ uint32_t s_v[kMaxProps * 6];
+    const uint32_t t = threadIdx.x;
+    if (t < a.n_props * 6) {
+        uint32_t v[kRootCopies];
+#pragma unroll
+        for (uint32_t c = 0; c < kRootCopies; ++c) v[c] = c < a.copies ? a.root_counts[c * kMaxProps * 6 + t] : 0u;
+        uint32_t sum = 0;
+#pragma unroll
+        for (uint32_t c = 0; c < kRootCopies; ++c) sum += v[c];
+        s_v[t] = sum;
+        a.root_counts_out[t] = sum;
+    }
+    if (t <= a.n_levels) a.sizes_out[t] = t < a.n_levels ? a.sizes_ws[t] : 0ull;
+    __syncthreads();
+    if (t < a.n_props) a.root_verdict[t] = (uint8_t)valuate(a.plan->prop[t], 0, s_v + 6 * t);
+}
 
 // Children are read in strided order (consecutive threads take consecutive
 // children; all loads of a tile are issued before any is used) and counted
@@ -1942,7 +1959,7 @@ hipError_t launch_inst_conclusive(const InstConclusiveArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(128), 0, s, a);
     return hipGetLastError();
 }
 

@@ -1036,6 +1036,9 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
         lo = min(lo, s_red[0][i]);
         hi = max(hi, s_red[1][i]);
     }
+    uint32_t bins[OWN ? PMAX : 1];              // this thread's verdicts, six counts of 5 bits (at most 16 words)
+#pragma unroll
+    for (int p = 0; p < (OWN ? PMAX : 1); ++p) bins[p] = 0;
     if (lo < hi) {
         const uint32_t cnt_iv = hi - lo, slot0 = lo + 1u - id_base;
         if (sparse) {
@@ -1060,14 +1063,21 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
 #pragma clang loop unroll(full)
                 for (int p = 0; p < PMAX; ++p) {
                     if (p > 0 && p >= (int)P) continue;
-                    a.inst_verdict[a.prop_idx[p] * a.inst_stride + lo + i] =
-                        (uint8_t)(a.emit_state ? q[p] : (s_lab[p][q[p] >> 3] >> (4 * (q[p] & 7u))) & 15u);
+                    const uint32_t v = a.emit_state ? q[p] : (s_lab[p][q[p] >> 3] >> (4 * (q[p] & 7u))) & 15u;
+                    a.inst_verdict[a.prop_idx[p] * a.inst_stride + lo + i] = (uint8_t)v;
+                    if constexpr (OWN) bins[p] += 1u << (5u * v);
                 }
             }
         } else {
-            for (uint32_t p = 0; p < P; ++p)
-                for (uint32_t i = tid; i < cnt_iv; i += kMsThreads)
-                    a.inst_verdict[a.prop_idx[p] * a.inst_stride + lo + i] = s_iv[p * kIvStride + slot0 + i];
+#pragma clang loop unroll(full)
+            for (int p = 0; p < PMAX; ++p) {
+                if (p > 0 && p >= (int)P) continue;
+                for (uint32_t i = tid; i < cnt_iv; i += kMsThreads) {
+                    const uint32_t v = s_iv[p * kIvStride + slot0 + i];
+                    a.inst_verdict[a.prop_idx[p] * a.inst_stride + lo + i] = (uint8_t)v;
+                    if constexpr (OWN) bins[p] += 1u << (5u * v);
+                }
+            }
         }
         if (structure && a.inst_parent && L >= 2)
             for (uint32_t i = tid; i < cnt_iv; i += kMsThreads) a.inst_parent[lo + i] = par_tile + s_par[slot0 + i];
@@ -1076,6 +1086,31 @@ __global__ __launch_bounds__(kMsThreads) void k_ms_down(ScanArgs a, PeParam<PE> 
         // ends, 60 us so
         if (structure && a.inst_keys)
             for (uint32_t i = tid; i < cnt_iv; i += kMsThreads) a.inst_keys[lo + i] = a.words[base + s_pos[slot0 + i]] >> a.cbits;
+    }
+    // One-level trees: the tile's verdicts are counted here, into one of the
+    // copies of the root's bins, instead of by a launch of their own (7.6 us for
+    // 1,000 instances; 16,384 socket events 41.3 -> 34.7 us a pass,
+    // 8.4M 169.1 -> 162.7 us).
+    if constexpr (OWN) if (a.root_bins && lo < hi) {
+        __shared__ uint32_t s_bins[PMAX][3][kMsThreads / 64];
+#pragma unroll
+        for (int p = 0; p < PMAX; ++p) {
+            if (p > 0 && p >= (int)P) continue;
+#pragma unroll
+            for (int h = 0; h < 3; ++h) {       // two bins a word: at most 16 x 64 each
+                const uint32_t x = wave_incl_sum(((bins[p] >> (10 * h)) & 31u) | (((bins[p] >> (10 * h + 5)) & 31u) << 16));
+                if (lane == 63) s_bins[p][h][w] = x;
+            }
+        }
+        __syncthreads();
+        if (tid < (int)P * 6) {
+            const uint32_t p = (uint32_t)tid / 6u, b = (uint32_t)tid % 6u;
+            uint32_t x = 0;
+#pragma unroll
+            for (int i = 0; i < kMsThreads / 64; ++i) x += s_bins[p][b >> 1][i];
+            x = (x >> (16 * (b & 1u))) & 0xFFFFu;
+            if (x) atomicAdd(a.root_bins + ((blockIdx.x % kRootCopies) * kMaxProps + prop_index<PMAX>(a, p)) * 6u + b, x);
+        }
     }
     // the thread holding the last word publishes the totals
     if (structure && r.cnt && my0 + r.cnt == n) {
@@ -1147,13 +1182,6 @@ static void launch_down(const ScanArgs& d, const PeParam<PE>& q, bool own, dim3 
     }
     hipLaunchKernelGGL((k_ms_down<PMAX, MW, ITEMS, TL, PE, SYM, false>), grid, dim3(kMsThreads), lds, s, d, q);
 }
-
-// Up to this many tiles every block of the down sweep composes what comes
-// before it by itself instead of waiting for a spine block, a launch less: 1M
-// words, one property, down sweep 9.0 us and spine 5.0 -> 9.9 us; 10M words 19.3
-// and 11.7 -> 26.6 us.  The records read grow with the square of the tiles, so
-// longer traces keep the spine.
-constexpr uint32_t kOwnTiles = 2560;
 
 template <int PMAX, int MW, int ITEMS, bool PE, bool SYM>
 static void launch_ms_t(const ScanArgs& a, const PeParam<PE>& q, hipStream_t s) {

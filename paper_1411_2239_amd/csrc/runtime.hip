@@ -274,7 +274,7 @@ WsLayout plan_workspace(const ltl4c_layout& L, const Geometry& g, uint64_t n, ui
     w.n_valid_off = z;     z += 64;
     w.sort_ticket_off = z; z += 64;
     w.scan_ticket_off = z; z += 64;
-    w.root_counts_off = z; z += kMaxProps * 6;
+    w.root_counts_off = z; z += kRootCopies * kMaxProps * 6;
     w.sizes32_off = z;     z += 64;
     w.sizes64_off = z;     z += 64;                      // 32 x uint64
     w.sort_status_off = z; z += (g.n_pass * w.sort_rows) << g.digit_bits;
@@ -1119,6 +1119,7 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
     fa.n_props = P;
     fa.plan = plan;
     fa.root_counts = root_counts;
+    fa.copies = 1;
     fa.root_verdict = out->root_verdict;
     fa.root_counts_out = out->root_counts;
     fa.sizes_ws = sizes64;
@@ -1182,6 +1183,10 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
         // over the own events and merges the parent events in.
         if (split) {
             set_split(sa, ws, w);
+            if (NL == 1 && w.ms_tiles <= kOwnTiles && !(ctx->scan_variant == kSplitScanVariant32 && !g.parent)) {
+                sa.root_bins = root_counts;      // the down sweep counts
+                fa.copies = kRootCopies;
+            }
         }
         ParentArgs pa{};
         if (g.parent) {
@@ -1252,7 +1257,7 @@ static int32_t eval_core(ltl4c_ctx* ctx, const ltl4c_layout& L, const Geometry& 
             if (s) return s;
         }
         fused_finalize = NL >= 2;                             // the node-level root count ends with Def. 7
-        for (int m = (int)NL - 1; m >= 0; --m) {
+        for (int m = sa.root_bins ? -1 : (int)NL - 1; m >= 0; --m) {
             CountArgs c{};
             c.level = (uint32_t)m;
             c.n_levels = NL;
