@@ -114,6 +114,9 @@ struct SortPassArgs {
     uint32_t* status;                // [tiles, then groups of tiles][buckets] look-back words
     uint32_t* ticket;
     const uint32_t* n_valid;         // non-null: words kept by the first pass (device)
+    // several sorts of the same size in one launch (blockIdx.y): steps from one to the next, in elements
+    uint64_t word_step, status_step;
+    uint32_t hist_step, ticket_step;
     uint32_t drop_excl;              // first pass: words with bit excl_shift set are dropped
     uint32_t excl_shift;
     uint32_t* err;
@@ -342,13 +345,9 @@ constexpr int kRankThreads = 256;
 constexpr int kRankItems = 16;
 constexpr int kRankTile = kRankThreads * kRankItems;
 constexpr int kRankSpineThreads = 1024;
-struct RankArgs {
-    const uint8_t* records;
-    uint64_t n;
-    uint32_t record_bytes;
-    uint32_t type_dw, type_shift, type_mask;
+struct RankLevel {
     uint32_t has_key[8];                 // bit t: events of type t carry this level's key
-    uint32_t level, key_dw, key_shift, key_mask;
+    uint32_t key_dw, key_shift, key_mask;
     uint64_t* words;                     // prep: value << 32 | event index
     uint32_t* hist;                      // prep: [kHistCopies][4][256] histograms of the value's bytes
     const uint64_t* sorted;              // the words after the radix passes over the value
@@ -357,6 +356,14 @@ struct RankArgs {
     uint32_t* n_distinct;                // number of distinct values
     uint32_t* rank;                      // [n] rank of every event's value
     uint32_t* uniq;                      // [n] value of every rank
+};
+struct RankArgs {
+    const uint8_t* records;
+    uint64_t n;
+    uint32_t record_bytes;
+    uint32_t type_dw, type_shift, type_mask;
+    uint32_t levels;                     // of this launch: blockIdx.y
+    RankLevel lv[kMaxLevels];
 };
 struct KeyValuesArgs {
     const uint64_t* packed;              // packed keys (or ranks) of instances or nodes
@@ -373,7 +380,7 @@ struct KeyValuesArgs {
 // Launchers (defined in kernels.hip, parent.hip and rank.hip).
 hipError_t launch_zero(const ZeroArgs& a, uint32_t blocks, hipStream_t s);
 hipError_t launch_classify(const ClassifyArgs& a, hipStream_t s);
-hipError_t launch_sort_pass(const SortPassArgs& a, int variant, uint32_t digit_bits, hipStream_t s);
+hipError_t launch_sort_pass(const SortPassArgs& a, int variant, uint32_t digit_bits, hipStream_t s, uint32_t sorts = 1);
 // Block and words per thread of a sort variant for n words, and its look-back.
 struct SortShape {
     uint32_t threads, items;

@@ -413,6 +413,13 @@ void k_sort_pass(SortPassArgs a) {
     __shared__ uint32_t s_tmp[2 * NB];
     __shared__ uint32_t s_tile;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if (blockIdx.y) {                          // (uniform) another sort of this launch
+        a.in += blockIdx.y * a.word_step;
+        a.out += blockIdx.y * a.word_step;
+        a.status += blockIdx.y * a.status_step;
+        a.hist += blockIdx.y * a.hist_step;
+        a.ticket += blockIdx.y * a.ticket_step;
+    }
     if (tid == 0) s_tile = atomicAdd(a.ticket, 1u);
     for (int i = tid; i < WAVES * B; i += THREADS) s_wcnt[i] = 0;
     __syncthreads();
@@ -1848,8 +1855,8 @@ uint64_t sort_status_rows(int variant, uint64_t n) {
 uint32_t sort_threads(int variant) { return sort_shape(variant, 0).threads; }
 
 template <int T, int I, bool G>
-static void launch_sort_t(const SortPassArgs& a, uint32_t digit_bits, hipStream_t s) {
-    const dim3 grid((a.n + T * I - 1) / (T * I)), block(T);
+static void launch_sort_t(const SortPassArgs& a, uint32_t digit_bits, hipStream_t s, uint32_t sorts) {
+    const dim3 grid((a.n + T * I - 1) / (T * I), sorts), block(T);
     if constexpr (T >= 512) {
         if (digit_bits == 9) {
             hipLaunchKernelGGL((k_sort_pass<T, I, 9, G>), grid, block, 0, s, a);
@@ -1859,30 +1866,30 @@ static void launch_sort_t(const SortPassArgs& a, uint32_t digit_bits, hipStream_
     hipLaunchKernelGGL((k_sort_pass<T, I, 8, G>), grid, block, 0, s, a);
 }
 
-hipError_t launch_sort_pass(const SortPassArgs& a, int variant, uint32_t digit_bits, hipStream_t s) {
+hipError_t launch_sort_pass(const SortPassArgs& a, int variant, uint32_t digit_bits, hipStream_t s, uint32_t sorts) {
     const SortShape sh = sort_shape(variant, a.n);
     if (digit_bits != 8 && !(digit_bits == 9 && sh.threads >= 512)) return hipErrorInvalidValue;
     if (sh.threads == 256) {
-        if (sh.items == 8) launch_sort_t<256, 8, false>(a, digit_bits, s);
-        else if (sh.items == 24) launch_sort_t<256, 24, false>(a, digit_bits, s);
-        else launch_sort_t<256, 16, false>(a, digit_bits, s);
+        if (sh.items == 8) launch_sort_t<256, 8, false>(a, digit_bits, s, sorts);
+        else if (sh.items == 24) launch_sort_t<256, 24, false>(a, digit_bits, s, sorts);
+        else launch_sort_t<256, 16, false>(a, digit_bits, s, sorts);
     } else if (sh.threads == 512) {
-        if (sh.items == 8) launch_sort_t<512, 8, false>(a, digit_bits, s);
-        else if (sh.items == 12) launch_sort_t<512, 12, false>(a, digit_bits, s);
-        else launch_sort_t<512, 16, false>(a, digit_bits, s);
+        if (sh.items == 8) launch_sort_t<512, 8, false>(a, digit_bits, s, sorts);
+        else if (sh.items == 12) launch_sort_t<512, 12, false>(a, digit_bits, s, sorts);
+        else launch_sort_t<512, 16, false>(a, digit_bits, s, sorts);
     } else if (!sh.grouped) {
-        launch_sort_t<1024, 16, false>(a, digit_bits, s);
+        launch_sort_t<1024, 16, false>(a, digit_bits, s, sorts);
     } else {
         switch (sh.items) {
-            case 2: launch_sort_t<1024, 2, true>(a, digit_bits, s); break;
-            case 4: launch_sort_t<1024, 4, true>(a, digit_bits, s); break;
-            case 6: launch_sort_t<1024, 6, true>(a, digit_bits, s); break;
-            case 8: launch_sort_t<1024, 8, true>(a, digit_bits, s); break;
-            case 10: launch_sort_t<1024, 10, true>(a, digit_bits, s); break;
-            case 12: launch_sort_t<1024, 12, true>(a, digit_bits, s); break;
-            case 13: launch_sort_t<1024, 13, true>(a, digit_bits, s); break;
-            case 14: launch_sort_t<1024, 14, true>(a, digit_bits, s); break;
-            default: launch_sort_t<1024, 16, true>(a, digit_bits, s); break;
+            case 2: launch_sort_t<1024, 2, true>(a, digit_bits, s, sorts); break;
+            case 4: launch_sort_t<1024, 4, true>(a, digit_bits, s, sorts); break;
+            case 6: launch_sort_t<1024, 6, true>(a, digit_bits, s, sorts); break;
+            case 8: launch_sort_t<1024, 8, true>(a, digit_bits, s, sorts); break;
+            case 10: launch_sort_t<1024, 10, true>(a, digit_bits, s, sorts); break;
+            case 12: launch_sort_t<1024, 12, true>(a, digit_bits, s, sorts); break;
+            case 13: launch_sort_t<1024, 13, true>(a, digit_bits, s, sorts); break;
+            case 14: launch_sort_t<1024, 14, true>(a, digit_bits, s, sorts); break;
+            default: launch_sort_t<1024, 16, true>(a, digit_bits, s, sorts); break;
         }
     }
     return hipGetLastError();

@@ -124,7 +124,7 @@ struct ltl4c_ctx {
     std::vector<ltl4c_property> props;
     std::map<std::vector<int32_t>, Plan*> plans;
     uint32_t* err_dev = nullptr;
-    uint32_t* err_host = nullptr;      // pinned: where ltl4c_wait has the error word copied to
+    uint32_t* err_host = nullptr;      // pinned: the error word (ltl4c_wait), from word 4 on distinct key counts
     int sort_variant = kDefaultSortVariant;
     int scan_variant = kDefaultScanVariant;
     uint64_t budget = ~0ull, used = 0;
@@ -387,27 +387,37 @@ struct RankRegion {
     uint64_t distinct_off;                // [4] distinct values per level
     uint64_t tile_cnt_off, tile_off_off;
     uint64_t rank_off[kMaxLevels], uniq_off[kMaxLevels];
-    uint64_t sort_rows;
+    uint64_t sort_rows, level_words, tiles;
+    uint64_t words_off, word_bytes;       // levels ranked together: two word buffers each
     uint64_t total;
 };
 
-RankRegion rank_region(const ltl4c_layout& L, uint64_t n, int sort_variant) {
+// together: all levels in the same launches, which takes word buffers and look-
+// back memory for each (short traces, whose passes mostly wait for latency;
+// one level after the other needs no more than the evaluation's own buffers).
+constexpr uint64_t kRankTogether = 4u << 20;
+RankRegion rank_region(const ltl4c_layout& L, uint64_t n, int sort_variant, bool together) {
     RankRegion r{};
+    const uint32_t sorts = together ? L.n_keys : 1u;
     r.sort_rows = sort_status_rows(sort_variant, n);
     r.hist_w = 0;
     r.ticket_w = kHistCopies * 4 * 256;
     r.status_w = r.ticket_w + 64;
-    r.zero_words = r.status_w + 4ull * r.sort_rows * 256;
+    r.level_words = r.status_w + 4ull * r.sort_rows * 256;
+    r.zero_words = sorts * r.level_words;
     uint64_t off = 0;
     r.zero_off = off;       off = align256(off + 4 * r.zero_words);
     r.distinct_off = off;   off = align256(off + 64);
-    const uint64_t tiles = std::max<uint64_t>(1, (n + kRankTile - 1) / kRankTile);
-    r.tile_cnt_off = off;   off = align256(off + 4 * tiles);
-    r.tile_off_off = off;   off = align256(off + 4 * tiles);
+    r.tiles = std::max<uint64_t>(1, (n + kRankTile - 1) / kRankTile);
+    r.tile_cnt_off = off;   off = align256(off + 4 * r.tiles * sorts);
+    r.tile_off_off = off;   off = align256(off + 4 * r.tiles * sorts);
     for (uint32_t m = 0; m < L.n_keys; ++m) {
         r.rank_off[m] = off; off = align256(off + 4 * std::max<uint64_t>(n, 1));
         r.uniq_off[m] = off; off = align256(off + 4 * std::max<uint64_t>(n, 1));
     }
+    r.words_off = off;
+    r.word_bytes = align256(8 * n + 256);
+    if (together) off += 2 * sorts * r.word_bytes;
     r.total = off;
     return r;
 }
@@ -1028,7 +1038,7 @@ uint64_t eval_ws_bytes(ltl4c_ctx* ctx, uint64_t n, const int32_t* props, int32_t
     const bool ranked = needs_ranks(ctx->layout, n);
     const ltl4c_layout L = ranked ? rank_sized(ctx->layout, n) : ctx->layout;
     Geometry g = geometry(L, 0, false, true, sort_threads(ctx->sort_variant) >= 512);
-    return (ranked ? rank_region(L, n, ctx->sort_variant).total : 0) +
+    return (ranked ? rank_region(L, n, ctx->sort_variant, n <= kRankTogether).total : 0) +
            plan_workspace(L, g, n, (uint32_t)n_props, (uint32_t)scan_groups(monitor_states(ctx, props, n_props)).size(),
                           ctx->sort_variant, ctx->scan_variant)
                .total;
@@ -1320,11 +1330,12 @@ static Plan host_plan(ltl4c_ctx* ctx, const int32_t* props, int32_t n_props) {
 // event i, and the value of every rank; the distinct counts land in the
 // ranking area for the host to read.
 static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* d_records, uint64_t n, uint8_t* area,
-                             const RankRegion& rr, uint64_t* wa, uint64_t* wb) {
+                             const RankRegion& rr, uint64_t* wa, uint64_t* wb, bool together) {
     const hipStream_t st = ctx->stream;
     uint32_t* z = reinterpret_cast<uint32_t*>(area + rr.zero_off);
+    const uint32_t sorts = together ? L.n_keys : 1u;
     int32_t s = LTL4C_OK;
-    for (uint32_t m = 0; m < L.n_keys && s == LTL4C_OK; ++m) {
+    for (uint32_t m0 = 0; m0 < L.n_keys && s == LTL4C_OK; m0 += sorts) {
         ZeroArgs za{z, nullptr, 0, rr.zero_words, 0};
         const uint32_t blocks = (uint32_t)std::min<uint64_t>(1024, (rr.zero_words + 255) / 256);
         s = launch(ctx, "zero", [&] { return launch_zero(za, blocks ? blocks : 1, st); });
@@ -1336,23 +1347,27 @@ static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* 
         ra.type_dw = L.type_offset / 4;
         ra.type_shift = (L.type_offset % 4) * 8;
         ra.type_mask = L.type_bytes == 4 ? 0xFFFFFFFFu : ((1u << (8 * L.type_bytes)) - 1u);
-        for (uint32_t t = 0; t < 256; ++t)
-            if ((L.key_present[t] >> m) & 1u) ra.has_key[t >> 5] |= 1u << (t & 31u);
-        ra.level = m;
-        ra.key_dw = L.key_offset[m] / 4;
-        ra.key_shift = (L.key_offset[m] % 4) * 8;
-        ra.key_mask = L.key_bytes[m] == 4 ? 0xFFFFFFFFu : ((1u << (8 * L.key_bytes[m])) - 1u);
-        ra.words = wa;
-        ra.hist = z + rr.hist_w;
-        ra.sorted = wa;
-        ra.tile_cnt = reinterpret_cast<uint32_t*>(area + rr.tile_cnt_off);
-        ra.tile_off = reinterpret_cast<uint32_t*>(area + rr.tile_off_off);
-        ra.n_distinct = reinterpret_cast<uint32_t*>(area + rr.distinct_off) + m;
-        ra.rank = reinterpret_cast<uint32_t*>(area + rr.rank_off[m]);
-        ra.uniq = reinterpret_cast<uint32_t*>(area + rr.uniq_off[m]);
+        ra.levels = sorts;
+        for (uint32_t k = 0; k < sorts; ++k) {
+            const uint32_t m = m0 + k;
+            RankLevel& l = ra.lv[k];
+            for (uint32_t t = 0; t < 256; ++t)
+                if ((L.key_present[t] >> m) & 1u) l.has_key[t >> 5] |= 1u << (t & 31u);
+            l.key_dw = L.key_offset[m] / 4;
+            l.key_shift = (L.key_offset[m] % 4) * 8;
+            l.key_mask = L.key_bytes[m] == 4 ? 0xFFFFFFFFu : ((1u << (8 * L.key_bytes[m])) - 1u);
+            l.words = together ? reinterpret_cast<uint64_t*>(area + rr.words_off + 2 * k * rr.word_bytes) : wa;
+            l.hist = z + k * rr.level_words + rr.hist_w;
+            l.sorted = l.words;
+            l.tile_cnt = reinterpret_cast<uint32_t*>(area + rr.tile_cnt_off) + k * rr.tiles;
+            l.tile_off = reinterpret_cast<uint32_t*>(area + rr.tile_off_off) + k * rr.tiles;
+            l.n_distinct = reinterpret_cast<uint32_t*>(area + rr.distinct_off) + m;
+            l.rank = reinterpret_cast<uint32_t*>(area + rr.rank_off[m]);
+            l.uniq = reinterpret_cast<uint32_t*>(area + rr.uniq_off[m]);
+        }
         s = launch(ctx, "rank", [&] { return launch_rank_prep(ra, st); });
-        uint64_t* in = wa;
-        uint64_t* outw = wb;
+        uint64_t* in = ra.lv[0].words;
+        uint64_t* outw = together ? in + rr.word_bytes / 8 : wb;
         for (uint32_t p = 0; p < 4 && s == LTL4C_OK; ++p) {
             SortPassArgs sa{};
             sa.in = in;
@@ -1364,8 +1379,12 @@ static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* 
             sa.hist_stride = 4 * 256;
             sa.status = z + rr.status_w + p * rr.sort_rows * 256;
             sa.ticket = z + rr.ticket_w + p;
+            sa.word_step = rr.word_bytes / 4;
+            sa.status_step = rr.level_words;
+            sa.hist_step = (uint32_t)rr.level_words;
+            sa.ticket_step = (uint32_t)rr.level_words;
             sa.err = ctx->err_dev;
-            s = launch(ctx, "rank", [&] { return launch_sort_pass(sa, ctx->sort_variant, 8, st); });
+            s = launch(ctx, "rank", [&] { return launch_sort_pass(sa, ctx->sort_variant, 8, st, sorts); });
             std::swap(in, outw);
         }
         if (s == LTL4C_OK) s = launch(ctx, "rank", [&] { return launch_rank_scan(ra, st); });
@@ -1445,19 +1464,24 @@ static int32_t eval_impl(ltl4c_ctx* ctx, const void* d_records, uint64_t n, cons
     Geometry g = geometry(L, 0, false, true, sort_threads(ctx->sort_variant) >= 512);
     const std::vector<ScanGroup> groups = scan_groups(monitor_states(ctx, props, n_props));
     WsLayout w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
-    uint64_t rbytes = ranked ? rank_region(L, n, ctx->sort_variant).total : 0;
+    bool together = n <= kRankTogether;
+    uint64_t rbytes = ranked ? rank_region(L, n, ctx->sort_variant, together).total : 0;
     if (ws_bytes < rbytes + w.total && sc.changed()) {
         // a workspace sized for the context's own schedule: run that one
         sc.revert();
         g = geometry(L, 0, false, true, sort_threads(ctx->sort_variant) >= 512);
         w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
-        rbytes = ranked ? rank_region(L, n, ctx->sort_variant).total : 0;
+        rbytes = ranked ? rank_region(L, n, ctx->sort_variant, together).total : 0;
     }
     if (ws_bytes < rbytes + w.total && ctx->sort_variant == kDefaultSortVariant) {
         // the largest tiles need the least look-back memory (the library's own scratch near its limit)
         ctx->sort_variant = kSmallSortVariant;
         w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
-        rbytes = ranked ? rank_region(L, n, ctx->sort_variant).total : 0;
+        rbytes = ranked ? rank_region(L, n, ctx->sort_variant, together).total : 0;
+    }
+    if (ranked && together && ws_bytes < rbytes + w.total) {
+        together = false;
+        rbytes = rank_region(L, n, ctx->sort_variant, together).total;
     }
     if (ws_bytes < rbytes + w.total) {
         if (!noalloc) return fail(LTL4C_ENOMEM, "workspace smaller than ltl4c_workspace_bytes()");
@@ -1482,13 +1506,15 @@ static int32_t eval_impl(ltl4c_ctx* ctx, const void* d_records, uint64_t n, cons
                                             "device: not under graph capture or without allocation");
         HIP_TRY(hipSetDevice(ctx->device));
         uint8_t* ws8 = static_cast<uint8_t*>(d_ws);
-        const RankRegion rr = rank_region(L, n, ctx->sort_variant);
+        const RankRegion rr = rank_region(L, n, ctx->sort_variant, together);
         uint64_t* wa = reinterpret_cast<uint64_t*>(ws8 + rr.total + w.words_a_off);
         uint64_t* wb = reinterpret_cast<uint64_t*>(ws8 + rr.total + w.words_b_off);
-        s = enqueue_ranks(ctx, ctx->layout, d_records, n, ws8, rr, wa, wb);
+        s = enqueue_ranks(ctx, ctx->layout, d_records, n, ws8, rr, wa, wb, together);
         if (s) return s;
-        uint32_t distinct[kMaxLevels] = {0, 0, 0, 0};
-        HIP_TRY(hipMemcpyAsync(distinct, ws8 + rr.distinct_off, sizeof distinct, hipMemcpyDeviceToHost, ctx->stream));
+        // (through pinned memory: a pageable destination is staged by the runtime)
+        if (!ctx->err_host) HIP_TRY(hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault));
+        const uint32_t* distinct = ctx->err_host + 4;
+        HIP_TRY(hipMemcpyAsync(ctx->err_host + 4, ws8 + rr.distinct_off, 4 * kMaxLevels, hipMemcpyDeviceToHost, ctx->stream));
         HIP_TRY(hipStreamSynchronize(ctx->stream));
         for (uint32_t m = 0; m < L.n_keys; ++m) {
             L.key_bits[m] = std::max<uint32_t>(1, bits_for(std::max<uint32_t>(distinct[m], 1)));
