@@ -446,12 +446,12 @@ int32_t ltl4c_group_restore(ltl4c_ctx *ctx, int32_t group, const void *host, uin
  * 4 = 512 x 8, 5 = 512 x 12, 6 (default) = 1024 threads x 2 to 16 words, as
  * many as fill the device's last round of tiles best for the trace's size.
  * The shapes of 512 and more threads sort 9-bit digits when that takes fewer
- * passes than 8-bit ones. */
+ * passes than 8-bit ones, 6 also 10-bit digits. */
 enum { LTL4C_OPT_SORT_TILE = 0, LTL4C_OPT_SCAN_TILE = 1 };
 /* LTL4C_OPT_SCAN_TILE: 4 (default) = the split map scan: per tile of 4096
- * words (256 threads x 16) a reduce launch, one spine launch over the tiles,
- * a down-sweep launch, no look-back; 5 = the same with 8192-word tiles
- * (256 x 32).  0..3 = the single-pass look-back map scan with tiles
+ * words (256 threads x 16) a reduce launch, where the trace has many tiles
+ * a launch or more for the tiles' prefixes, and a down-sweep launch, no
+ * look-back; 5 = the same with 8192-word tiles (256 x 32).  0..3 = the single-pass look-back map scan with tiles
  * of 0 = 256 threads x 16 words, 1 = 512 x 16, 2 = 1024 x 16, or 3 = per
  * launch: 1024 x 16 when a launch's maps take at most 4 dwords per event (one
  * or two properties of at most 8 states, or one of at most 16), else

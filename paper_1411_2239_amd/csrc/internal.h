@@ -11,6 +11,7 @@ constexpr int kMaxLevels = 4;
 constexpr int kStates = 16;          // monitor states, at most (a map holds one byte per state)
 constexpr int kRadixBits = 8;
 constexpr int kRadixBitsWide = 9;        // digit of the passes of 512-thread tiles, when it saves a pass
+constexpr int kRadixBitsWidest = 10;    // digit of the 1024-thread tiles, when it saves one more
 constexpr int kHistWords = 4096;         // classify's histograms: n_pass << digit bits, at most
 constexpr uint32_t kHistCopies = 4;      // of them in memory, for traces below kShortTrace events
 constexpr uint64_t kShortTrace = 6000000;
@@ -71,7 +72,7 @@ struct ClassifyArgs {
     uint32_t ibits;                  // trace index bits between the class and the key (0: none)
     uint32_t excl_shift;             // bit set in the word of an excluded event
     uint32_t n_pass;                 // radix passes whose histograms are built here
-    uint32_t digit_bits;             // radix digit width of the kernel (8 or 9): the histograms' stride
+    uint32_t digit_bits;             // radix digit width of the kernel (8 to 10): the histograms' stride
     uint32_t digit_step;             // bits of each digit (at most digit_bits)
     uint32_t sort_shift;             // lowest sorted bit
     const Plan* plan;
@@ -387,7 +388,7 @@ struct SortShape {
     bool grouped;
 };
 SortShape sort_shape(int variant, uint64_t n);
-uint32_t sort_threads(int variant);
+uint32_t sort_digit_bits(int variant);   // widest digit its tiles sort
 uint64_t sort_status_rows(int variant, uint64_t n);   // look-back rows of a pass over up to n words
 constexpr int kSortVariants = 7;
 constexpr int kDefaultSortVariant = 6;     // 1024 threads x 2..16 words, fitted to the trace

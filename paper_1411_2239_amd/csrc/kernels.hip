@@ -5,7 +5,7 @@
 //                class) and packed binding key; builds the radix histograms
 //                of every sort pass in the same read.
 //   k_sort_pass  one stable LSD radix pass (ParallelSort of Algorithm 1) on
-//                8- or 9-bit digits: single-pass "onesweep" ranking with wave
+//                8- to 10-bit digits: single-pass "onesweep" ranking with wave
 //                ballots, LDS-staged scatter and decoupled look-back across
 //                tiles; the first pass may drop events that join no cluster.
 //   k_scan       Distribute / ProcessBuffer of Algorithm 1 as a flat scan:
@@ -398,7 +398,7 @@ void k_sort_pass(SortPassArgs a) {
     constexpr int WAVES = THREADS / 64;
     constexpr int PHASES = TILE <= 16384 ? 1 : (TILE + 8191) / 8192;
     constexpr int CHUNK = TILE / PHASES;
-    // 512 buckets: the per-wave counters and the key buffer share LDS (keys
+    // 512 and more buckets: the per-wave counters and the key buffer share LDS (keys
     // are placed once every position is known), which keeps two 512 x 16
     // blocks on a CU
     constexpr bool kShare = RB > 8;
@@ -1855,7 +1855,10 @@ uint64_t sort_status_rows(int variant, uint64_t n) {
     return tiles;
 }
 
-uint32_t sort_threads(int variant) { return sort_shape(variant, 0).threads; }
+uint32_t sort_digit_bits(int variant) {
+    if (variant == kDefaultSortVariant) return kRadixBitsWidest;
+    return sort_shape(variant, 0).threads >= 512 ? kRadixBitsWide : kRadixBits;
+}
 
 template <int T, int I, bool G>
 static void launch_sort_t(const SortPassArgs& a, uint32_t digit_bits, hipStream_t s, uint32_t sorts) {
@@ -1866,12 +1869,18 @@ static void launch_sort_t(const SortPassArgs& a, uint32_t digit_bits, hipStream_
             return;
         }
     }
+    if constexpr (T >= 1024) {
+        if (digit_bits == 10) {
+            hipLaunchKernelGGL((k_sort_pass<T, I, 10, G>), grid, block, 0, s, a);
+            return;
+        }
+    }
     hipLaunchKernelGGL((k_sort_pass<T, I, 8, G>), grid, block, 0, s, a);
 }
 
 hipError_t launch_sort_pass(const SortPassArgs& a, int variant, uint32_t digit_bits, hipStream_t s, uint32_t sorts) {
     const SortShape sh = sort_shape(variant, a.n);
-    if (digit_bits != 8 && !(digit_bits == 9 && sh.threads >= 512)) return hipErrorInvalidValue;
+    if (digit_bits < 8 || digit_bits > sort_digit_bits(variant)) return hipErrorInvalidValue;
     if (sh.threads == 256) {
         if (sh.items == 8) launch_sort_t<256, 8, false>(a, digit_bits, s, sorts);
         else if (sh.items == 24) launch_sort_t<256, 24, false>(a, digit_bits, s, sorts);

@@ -6,13 +6,13 @@
 //           the block scans the threads in order; the tile's map per property
 //           and its head counts per level go to `agg`, every thread's
 //           exclusive prefix within the tile to `trec`;
-//   spine   exclusive prefixes of the tile records in tile order: one block,
-//           or, for many tiles, chunk compositions, their scan and the tile
-//           prefixes of every chunk (three launches);
+//   spine   exclusive prefixes of the tile records in tile order, in a few
+//           launches of their own, or, where every block can read the records
+//           before it (kOwnTiles), by the blocks of the down sweep themselves;
 //   down    per tile: every thread starts from its prefix (tile prefix, then
 //           its own), steps its states word by word and writes instance
 //           verdicts, parents, numbering and nodes (and, on request, the
-//           verdict timeline).
+//           verdict timeline; a one-level tree's verdicts are counted here).
 // Words are read as 16 or 32 consecutive 64-bit words per thread with 16-byte
 // loads (no LDS staging).  The first reduce writes one descriptor byte per word
 // (class, head and level-head flags); the down sweep and the launches of

@@ -144,7 +144,7 @@ namespace {
 struct Geometry {
     uint32_t cbits, key_bits_total, sort_bits, n_pass;
     uint32_t ibits;                         // trace index bits between class and key (per-event verdicts)
-    uint32_t digit_bits;                    // radix digit width: 8, or 9 when that saves a pass
+    uint32_t digit_bits;                    // radix digit width: 8, or 9 or 10 when that saves a pass
     uint32_t digit_step;                    // bits of each digit: the sorted bits spread over the passes
     bool compact;                           // the first radix pass drops excluded events
     uint32_t stream_bits;                   // stream / trace id above the keys
@@ -159,10 +159,10 @@ struct Geometry {
 // of traces: one subtree per trace); otherwise it only separates streams.
 // compact: excluded events are dropped by the first radix pass instead of
 // being sorted behind the others on an extra key bit (the consumers then read
-// the kept count on the device).  wide: the sort variant has a thread per
-// bucket for 9-bit digits.
+// the kept count on the device).  widest: the sort variant has a thread per
+// bucket for digits of that many bits.
 Geometry geometry(const ltl4c_layout& L, uint32_t stream_bits = 0, bool stream_is_level = false,
-                  bool compact = false, bool wide = false) {
+                  bool compact = false, uint32_t widest = kRadixBits) {
     Geometry g{};
     g.cbits = bits_for(L.n_classes);
     // parent events sort after all own events on a kind bit above the keys,
@@ -184,13 +184,25 @@ Geometry geometry(const ltl4c_layout& L, uint32_t stream_bits = 0, bool stream_i
         if ((L.key_present[t] & need) != need) g.excl = true;
     g.compact = compact && g.excl && kb > 0;
     g.sort_bits = kb + (g.excl && !g.compact ? 1u : 0u);
-    const uint32_t p8 = (g.sort_bits + kRadixBits - 1) / kRadixBits;
-    const uint32_t p9 = (g.sort_bits + kRadixBitsWide - 1) / kRadixBitsWide;
-    g.digit_bits = wide && p9 < p8 && (p9 << kRadixBitsWide) <= (uint32_t)kHistWords ? kRadixBitsWide : kRadixBits;
-    g.n_pass = (g.sort_bits + g.digit_bits - 1) / g.digit_bits;
+    // The narrowest digit among those with the fewest passes.  10-bit digits
+    // have one bucket per thread of the largest blocks and cost a pass 0-20 %
+    // more than 9-bit ones, so one pass in place of two, two of three and three
+    // of four pay (all passes at 0.3M, 3M and 10M events, 10-bit keys: 13.9,
+    // 24.2, 62.8 us against 22.2, 41.8, 102.5; 20-bit: 27.6, 50.2, 124.2
+    // against 33.9, 61.7, 154.6; 30-bit: 42.3, 72.7, 189.3 against 45.0, 83.1,
+    // 206.1), but four of five do not (a call of 40M events 1,474 -> 1,501).
+    g.digit_bits = kRadixBits;
+    g.n_pass = (g.sort_bits + kRadixBits - 1) / kRadixBits;
+    for (uint32_t d = kRadixBits + 1; d <= widest; ++d) {
+        const uint32_t passes = (g.sort_bits + d - 1) / d;
+        if (passes >= g.n_pass || (passes << d) > (uint32_t)kHistWords) continue;
+        if (d == (uint32_t)kRadixBitsWidest && passes > 3) continue;
+        g.digit_bits = d;
+        g.n_pass = passes;
+    }
     // equal digits: a last digit of a few bits has every block of classify add
-    // to the same few bins (8.4M events with 10-bit keys: 8 + 2 bits 176.4 us a
-    // pass, 5 + 5 bits 169.1)
+    // to the same few bins (a call of 8.4M events with 10-bit keys in two passes:
+    // 8 + 2 bits 176.4 us, 5 + 5 bits 169.1)
     g.digit_step = (g.sort_bits + g.n_pass - 1) / std::max<uint32_t>(g.n_pass, 1);
     return g;
 }
@@ -784,7 +796,7 @@ int32_t group_configure(ltl4c_ctx* ctx, GroupHost& G, const int32_t* props, int3
     // (the look-back scan takes excluded events sorted behind the others, the
     // split scan without them)
     const bool split = ctx->scan_variant == kSplitScanVariant || ctx->scan_variant == kSplitScanVariant32;
-    G.g = geometry(L, sb, false, split, sort_threads(ctx->sort_variant) >= 512);
+    G.g = geometry(L, sb, false, split, sort_digit_bits(ctx->sort_variant));
     if (G.g.cbits + G.g.key_bits_total + (G.g.excl ? 1 : 0) > 63)
         return fail(LTL4C_EUNSUPPORTED, "stream id, keys and class bits exceed 63 bits");
     G.sort_variant = ctx->sort_variant;
@@ -1037,7 +1049,7 @@ struct SchedScope {
 uint64_t eval_ws_bytes(ltl4c_ctx* ctx, uint64_t n, const int32_t* props, int32_t n_props) {
     const bool ranked = needs_ranks(ctx->layout, n);
     const ltl4c_layout L = ranked ? rank_sized(ctx->layout, n) : ctx->layout;
-    Geometry g = geometry(L, 0, false, true, sort_threads(ctx->sort_variant) >= 512);
+    Geometry g = geometry(L, 0, false, true, sort_digit_bits(ctx->sort_variant));
     return (ranked ? rank_region(L, n, ctx->sort_variant, n <= kRankTogether).total : 0) +
            plan_workspace(L, g, n, (uint32_t)n_props, (uint32_t)scan_groups(monitor_states(ctx, props, n_props)).size(),
                           ctx->sort_variant, ctx->scan_variant)
@@ -1461,7 +1473,7 @@ static int32_t eval_impl(ltl4c_ctx* ctx, const void* d_records, uint64_t n, cons
     if (n > 0 && (reinterpret_cast<uintptr_t>(d_records) & 3))
         return fail(LTL4C_EINVAL, "records must be 4-byte aligned");
     SchedScope sc(ctx, find_sched(ctx, shape_of(ctx, 0, n, 0, props, n_props)));
-    Geometry g = geometry(L, 0, false, true, sort_threads(ctx->sort_variant) >= 512);
+    Geometry g = geometry(L, 0, false, true, sort_digit_bits(ctx->sort_variant));
     const std::vector<ScanGroup> groups = scan_groups(monitor_states(ctx, props, n_props));
     WsLayout w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
     bool together = n <= kRankTogether;
@@ -1469,13 +1481,14 @@ static int32_t eval_impl(ltl4c_ctx* ctx, const void* d_records, uint64_t n, cons
     if (ws_bytes < rbytes + w.total && sc.changed()) {
         // a workspace sized for the context's own schedule: run that one
         sc.revert();
-        g = geometry(L, 0, false, true, sort_threads(ctx->sort_variant) >= 512);
+        g = geometry(L, 0, false, true, sort_digit_bits(ctx->sort_variant));
         w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
         rbytes = ranked ? rank_region(L, n, ctx->sort_variant, together).total : 0;
     }
     if (ws_bytes < rbytes + w.total && ctx->sort_variant == kDefaultSortVariant) {
         // the largest tiles need the least look-back memory (the library's own scratch near its limit)
         ctx->sort_variant = kSmallSortVariant;
+        g = geometry(L, 0, false, true, sort_digit_bits(ctx->sort_variant));
         w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
         rbytes = ranked ? rank_region(L, n, ctx->sort_variant, together).total : 0;
     }
@@ -1522,10 +1535,15 @@ static int32_t eval_impl(ltl4c_ctx* ctx, const void* d_records, uint64_t n, cons
             value_of[m] = reinterpret_cast<const uint32_t*>(ws8 + rr.uniq_off[m]);
         }
         // the evaluation proper, on the ranks, in the workspace after the ranking area
-        g = geometry(L, 0, false, true, sort_threads(ctx->sort_variant) >= 512);
-        w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
+        // (fewer key bits than it was sized for may take wider digits and so
+        // more look-back memory: narrower ones then)
         d_ws = ws8 + rr.total;
         ws_bytes -= rr.total;
+        for (uint32_t d = sort_digit_bits(ctx->sort_variant); d >= (uint32_t)kRadixBits; --d) {
+            g = geometry(L, 0, false, true, d);
+            w = plan_workspace(L, g, n, P, (uint32_t)groups.size(), ctx->sort_variant, ctx->scan_variant);
+            if (w.total <= ws_bytes) break;
+        }
         if (g.cbits + g.key_bits_total + (g.excl ? 1 : 0) > 63)
             return fail(LTL4C_EUNSUPPORTED, "even ranked, the binding key plus class bits exceed 63 bits");
     }
@@ -1622,7 +1640,7 @@ int32_t batch_layout(ltl4c_ctx* ctx, uint64_t n, int32_t n_traces, uint32_t P, u
     if (L.parent_events) return fail(LTL4C_EUNSUPPORTED, "batches do not take layouts with parent events");
     if (n > LTL4C_MAX_EVENTS) return fail(LTL4C_EUNSUPPORTED, "too many events for one call");
     b->g = geometry(L, std::max<uint32_t>(1, bits_for((uint32_t)n_traces)), true, true,
-                    sort_threads(ctx->sort_variant) >= 512);
+                    sort_digit_bits(ctx->sort_variant));
     if (b->g.cbits + b->g.key_bits_total + (b->g.excl ? 1 : 0) > 63)
         return fail(LTL4C_EUNSUPPORTED, "trace id, keys and class bits exceed 63 bits");
     b->w = plan_workspace(L, b->g, n, P, n_scan_groups, ctx->sort_variant, ctx->scan_variant);
