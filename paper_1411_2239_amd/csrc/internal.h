@@ -354,7 +354,7 @@ struct RankLevel {
     const uint64_t* sorted;              // the words after the radix passes over the value
     uint32_t* tile_cnt;                  // [tiles] distinct-value heads per tile
     uint32_t* tile_off;                  // [tiles] heads before each tile
-    uint32_t* n_distinct;                // number of distinct values
+    uint32_t* n_distinct;                // number of distinct values (pinned host memory)
     uint32_t* rank;                      // [n] rank of every event's value
     uint32_t* uniq;                      // [n] value of every rank
 };
@@ -430,7 +430,7 @@ hipError_t launch_parent_tree(const ParentArgs& a, uint32_t level0, uint32_t nle
 hipError_t launch_parent_affix(const ParentArgs& a, uint64_t max_entries, hipStream_t s);
 hipError_t launch_parent_bounds(const ParentArgs& a, uint64_t max_own, hipStream_t s);
 hipError_t launch_rank_prep(const RankArgs& a, hipStream_t s);
-hipError_t launch_rank_scan(const RankArgs& a, hipStream_t s);
+hipError_t launch_rank_scan(const RankArgs& a, hipEvent_t counted, hipStream_t s);   // counted: recorded once n_distinct is written
 hipError_t launch_key_values(const KeyValuesArgs& a, uint64_t max_n, hipStream_t s);
 
 }  // namespace ltl4c

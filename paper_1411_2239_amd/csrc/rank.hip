@@ -122,7 +122,10 @@ __global__ __launch_bounds__(kRankSpineThreads) void k_rank_spine(RankArgs a, ui
         l.tile_off[t] = s;
         s += l.tile_cnt[t];
     }
-    if (threadIdx.x == 0) *l.n_distinct = total;
+    // (straight into the host's memory: it waits for this launch only, and plans
+    // and enqueues the evaluation while k_rank_apply runs: 1.5M events with two
+    // ranked levels 338.8 us a call with a copy after k_rank_apply, 326.6 so)
+    if (threadIdx.x == 0) __hip_atomic_store(l.n_distinct, total, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 __global__ __launch_bounds__(kRankThreads) void k_rank_apply(RankArgs a) {
@@ -166,11 +169,15 @@ hipError_t launch_rank_prep(const RankArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_rank_scan(const RankArgs& a, hipStream_t s) {
+hipError_t launch_rank_scan(const RankArgs& a, hipEvent_t counted, hipStream_t s) {
     const uint32_t tiles = (uint32_t)((a.n + kRankTile - 1) / kRankTile);
-    if (tiles == 0) return hipSuccess;
+    if (tiles == 0) return counted ? hipEventRecord(counted, s) : hipSuccess;
     hipLaunchKernelGGL(k_rank_tiles, dim3(tiles, a.levels), dim3(kRankThreads), 0, s, a);
     hipLaunchKernelGGL(k_rank_spine, dim3(1, a.levels), dim3(kRankSpineThreads), 0, s, a, tiles);
+    if (counted) {
+        const hipError_t e = hipEventRecord(counted, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_rank_apply, dim3(tiles, a.levels), dim3(kRankThreads), 0, s, a);
     return hipGetLastError();
 }

@@ -131,6 +131,7 @@ struct ltl4c_ctx {
     uint32_t* batch_chunk_dev = nullptr;      // trace table of ltl4c_eval_batch
     uint32_t* batch_chunk_host = nullptr;     // pinned staging for it
     hipEvent_t batch_ev = nullptr;
+    hipEvent_t rank_ev = nullptr;      // the distinct key counts are in err_host
     std::vector<struct GroupHost*> groups;
     bool prof = false;
     std::vector<Timed> timed;
@@ -396,7 +397,6 @@ ltl4c_layout rank_sized(const ltl4c_layout& L, uint64_t n) {
 struct RankRegion {
     uint64_t zero_off, zero_words;        // histograms [kHistCopies][4][256], tickets, look-back status [4][tiles][256]
     uint64_t hist_w, ticket_w, status_w;  // word offsets inside the zero block
-    uint64_t distinct_off;                // [4] distinct values per level
     uint64_t tile_cnt_off, tile_off_off;
     uint64_t rank_off[kMaxLevels], uniq_off[kMaxLevels];
     uint64_t sort_rows, level_words, tiles;
@@ -419,7 +419,6 @@ RankRegion rank_region(const ltl4c_layout& L, uint64_t n, int sort_variant, bool
     r.zero_words = sorts * r.level_words;
     uint64_t off = 0;
     r.zero_off = off;       off = align256(off + 4 * r.zero_words);
-    r.distinct_off = off;   off = align256(off + 64);
     r.tiles = std::max<uint64_t>(1, (n + kRankTile - 1) / kRankTile);
     r.tile_cnt_off = off;   off = align256(off + 4 * r.tiles * sorts);
     r.tile_off_off = off;   off = align256(off + 4 * r.tiles * sorts);
@@ -899,6 +898,7 @@ int32_t ltl4c_destroy(ltl4c_ctx* ctx) {
     (void)hipFree(ctx->batch_chunk_dev);
     (void)hipHostFree(ctx->batch_chunk_host);
     if (ctx->batch_ev) (void)hipEventDestroy(ctx->batch_ev);
+    if (ctx->rank_ev) (void)hipEventDestroy(ctx->rank_ev);
     for (auto& t : ctx->timed) {
         (void)hipEventDestroy(t.start);
         (void)hipEventDestroy(t.stop);
@@ -1339,8 +1339,8 @@ static Plan host_plan(ltl4c_ctx* ctx, const int32_t* props, int32_t n_props) {
 }
 
 // Dense ranks of every level's key values (see rank.hip): rank[m][i] for
-// event i, and the value of every rank; the distinct counts land in the
-// ranking area for the host to read.
+// event i, and the value of every rank; the distinct counts land in
+// err_host, where the host reads them after rank_ev.
 static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* d_records, uint64_t n, uint8_t* area,
                              const RankRegion& rr, uint64_t* wa, uint64_t* wb, bool together) {
     const hipStream_t st = ctx->stream;
@@ -1373,7 +1373,7 @@ static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* 
             l.sorted = l.words;
             l.tile_cnt = reinterpret_cast<uint32_t*>(area + rr.tile_cnt_off) + k * rr.tiles;
             l.tile_off = reinterpret_cast<uint32_t*>(area + rr.tile_off_off) + k * rr.tiles;
-            l.n_distinct = reinterpret_cast<uint32_t*>(area + rr.distinct_off) + m;
+            l.n_distinct = ctx->err_host + 4 + m;
             l.rank = reinterpret_cast<uint32_t*>(area + rr.rank_off[m]);
             l.uniq = reinterpret_cast<uint32_t*>(area + rr.uniq_off[m]);
         }
@@ -1399,7 +1399,7 @@ static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* 
             s = launch(ctx, "rank", [&] { return launch_sort_pass(sa, ctx->sort_variant, 8, st, sorts); });
             std::swap(in, outw);
         }
-        if (s == LTL4C_OK) s = launch(ctx, "rank", [&] { return launch_rank_scan(ra, st); });
+        if (s == LTL4C_OK) s = launch(ctx, "rank", [&] { return launch_rank_scan(ra, m0 + sorts >= L.n_keys ? ctx->rank_ev : nullptr, st); });
     }
     return s;
 }
@@ -1522,13 +1522,13 @@ static int32_t eval_impl(ltl4c_ctx* ctx, const void* d_records, uint64_t n, cons
         const RankRegion rr = rank_region(L, n, ctx->sort_variant, together);
         uint64_t* wa = reinterpret_cast<uint64_t*>(ws8 + rr.total + w.words_a_off);
         uint64_t* wb = reinterpret_cast<uint64_t*>(ws8 + rr.total + w.words_b_off);
+        if (!ctx->err_host) HIP_TRY(hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault));
+        if (!ctx->rank_ev) HIP_TRY(hipEventCreateWithFlags(&ctx->rank_ev, hipEventDisableTiming));
+        std::memset(ctx->err_host + 4, 0, 4 * kMaxLevels);
         s = enqueue_ranks(ctx, ctx->layout, d_records, n, ws8, rr, wa, wb, together);
         if (s) return s;
-        // (through pinned memory: a pageable destination is staged by the runtime)
-        if (!ctx->err_host) HIP_TRY(hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault));
+        HIP_TRY(hipEventSynchronize(ctx->rank_ev));
         const uint32_t* distinct = ctx->err_host + 4;
-        HIP_TRY(hipMemcpyAsync(ctx->err_host + 4, ws8 + rr.distinct_off, 4 * kMaxLevels, hipMemcpyDeviceToHost, ctx->stream));
-        HIP_TRY(hipStreamSynchronize(ctx->stream));
         for (uint32_t m = 0; m < L.n_keys; ++m) {
             L.key_bits[m] = std::max<uint32_t>(1, bits_for(std::max<uint32_t>(distinct[m], 1)));
             rank_of[m] = reinterpret_cast<const uint32_t*>(ws8 + rr.rank_off[m]);
