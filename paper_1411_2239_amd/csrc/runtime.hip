@@ -1380,7 +1380,7 @@ static int32_t enqueue_ranks(ltl4c_ctx* ctx, const ltl4c_layout& L, const void* 
         s = launch(ctx, "rank", [&] { return launch_rank_prep(ra, st); });
         uint64_t* in = ra.lv[0].words;
         uint64_t* outw = together ? in + rr.word_bytes / 8 : wb;
-        for (uint32_t p = 0; p < 4 && s == LTL4C_OK; ++p) {
+        for (uint32_t p = 0; p < 4 && n > 0 && s == LTL4C_OK; ++p) {
             SortPassArgs sa{};
             sa.in = in;
             sa.out = outw;
