@@ -77,8 +77,9 @@ typedef struct ltl4c_ctx ltl4c_ctx;
  * set of value vectors of Eq. 5 only contains complete vectors).
  *
  * key_bits[m] (1..32) is the declared width of key m: every key value must be
- * below 2^key_bits[m].  A wider value is detected on the device and reported
- * as LTL4C_ERANGE by ltl4c_wait().  The composite binding key (key 0 in the
+ * below 2^key_bits[m].  A wider value is detected on the device, reported as
+ * LTL4C_ERANGE by ltl4c_wait() and cut to its low key_bits[m] bits, so that its
+ * event stays in its trace or stream.  The composite binding key (key 0 in the
  * most significant bits) is packed into a 64-bit sort word with the class
  * bits (and, when asked for, the trace index and the parent-event kind bit)
  * and an exclusion bit.  When the declared widths do not fit 63 bits,

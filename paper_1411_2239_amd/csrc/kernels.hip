@@ -241,10 +241,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
 #pragma unroll
         for (int m = 0; m < kMaxLevels; ++m) {
             if (m < nk) {
+                // A value wider than declared is reported and cut to its
+                // width: its other bits would reach the fields above (the
+                // stream or trace id, the parent kind, the exclusion bit), and
+                // an event counted as one thing here would be sorted as another.
                 const uint32_t b = a.key_bits[m];
                 const uint32_t v = par && m + 1 == nk ? 0u : a.rank[m] ? a.rank[m][i] : f[m];
                 over |= b < 32 ? (v >> b) : 0u;
-                key = (key << b) | v;
+                key = (key << b) | (v & (0xFFFFFFFFu >> (32u - b)));
             }
         }
         if (ok && over) err |= kErrRange;

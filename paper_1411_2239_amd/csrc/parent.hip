@@ -210,7 +210,9 @@ __global__ __launch_bounds__(kPeThreads) void k_pe_bounds(ParentArgs a) {
         if ((tid & 63u) == 0) s_part[wave] = b;
     }
     __syncthreads();
-    const uint32_t b0 = s_part[0], m = s_part[1] - b0;
+    // (own events in order give s_part[1] >= b0; m bounds every read below, so it
+    // does not rest on that)
+    const uint32_t b0 = s_part[0], m = max(s_part[1], b0) - b0;
     const uint64_t my0 = base + (uint64_t)tid * kPeItems;
     const uint32_t cnt = my0 < n_own ? (uint32_t)min<uint64_t>(kPeItems, n_own - my0) : 0u;
     if (m <= kPeStage) {
