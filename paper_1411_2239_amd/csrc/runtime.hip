@@ -125,6 +125,7 @@ struct ltl4c_ctx {
     std::map<std::vector<int32_t>, Plan*> plans;
     uint32_t* err_dev = nullptr;
     uint32_t* err_host = nullptr;      // pinned: the error word (ltl4c_wait), from word 4 on distinct key counts
+    bool moved = false;                // the stream was changed since the last ltl4c_wait
     int sort_variant = kDefaultSortVariant;
     int scan_variant = kDefaultScanVariant;
     uint64_t budget = ~0ull, used = 0;
@@ -920,7 +921,9 @@ int32_t ltl4c_destroy(ltl4c_ctx* ctx) {
 
 int32_t ltl4c_set_stream(ltl4c_ctx* ctx, void* hip_stream) {
     if (!ctx) return fail(LTL4C_EINVAL, "ctx is NULL");
-    ctx->stream = reinterpret_cast<hipStream_t>(hip_stream);
+    const hipStream_t to = reinterpret_cast<hipStream_t>(hip_stream);
+    ctx->moved = ctx->moved || to != ctx->stream;
+    ctx->stream = to;
     return LTL4C_OK;
 }
 
@@ -1780,11 +1783,20 @@ int32_t ltl4c_eval_batch(ltl4c_ctx* ctx, const void* d_records, const uint64_t* 
 int32_t ltl4c_wait(ltl4c_ctx* ctx) {
     if (!ctx) return fail(LTL4C_EINVAL, "ctx is NULL");
     HIP_TRY(hipSetDevice(ctx->device));
-    // the error word follows the work on the stream into pinned memory: one wait for both
-    if (!ctx->err_host) HIP_TRY(hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault));
-    HIP_TRY(hipMemcpyAsync(ctx->err_host, ctx->err_dev, 4, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    const uint32_t err = *ctx->err_host;
+    uint32_t err = 0;
+    if (ctx->moved) {
+        // work since the last wait may be on a stream before this one: a blocking
+        // copy also follows the null stream and the streams that wait for it
+        HIP_TRY(hipStreamSynchronize(ctx->stream));
+        HIP_TRY(hipMemcpy(&err, ctx->err_dev, 4, hipMemcpyDeviceToHost));
+        ctx->moved = false;
+    } else {
+        // the error word follows the work on the stream into pinned memory: one wait for both
+        if (!ctx->err_host) HIP_TRY(hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault));
+        HIP_TRY(hipMemcpyAsync(ctx->err_host, ctx->err_dev, 4, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(hipStreamSynchronize(ctx->stream));
+        err = *ctx->err_host;
+    }
     if (err) {
         HIP_TRY(hipMemset(ctx->err_dev, 0, 4));
         if (err & kErrSpin) return fail(LTL4C_EDEVICE, "a look-back wait exceeded its bound");
