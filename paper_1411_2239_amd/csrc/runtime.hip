@@ -880,8 +880,11 @@ int32_t ltl4c_create(ltl4c_ctx** out, int32_t device) {
     ctx->device = device;
     hipError_t e = hipMalloc(&ctx->err_dev, 256);
     if (e == hipSuccess) e = hipMemset(ctx->err_dev, 0, 256);
+    if (e == hipSuccess) e = hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault);
     if (e == hipSuccess) e = scratch_address(device, &ctx->scratch);
     if (e != hipSuccess) {
+        (void)hipHostFree(ctx->err_host);
+        (void)hipFree(ctx->err_dev);
         delete ctx;
         return fail(LTL4C_EDEVICE, std::string("context allocation: ") + hipGetErrorString(e));
     }
@@ -1525,7 +1528,6 @@ static int32_t eval_impl(ltl4c_ctx* ctx, const void* d_records, uint64_t n, cons
         const RankRegion rr = rank_region(L, n, ctx->sort_variant, together);
         uint64_t* wa = reinterpret_cast<uint64_t*>(ws8 + rr.total + w.words_a_off);
         uint64_t* wb = reinterpret_cast<uint64_t*>(ws8 + rr.total + w.words_b_off);
-        if (!ctx->err_host) HIP_TRY(hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault));
         if (!ctx->rank_ev) HIP_TRY(hipEventCreateWithFlags(&ctx->rank_ev, hipEventDisableTiming));
         std::memset(ctx->err_host + 4, 0, 4 * kMaxLevels);
         s = enqueue_ranks(ctx, ctx->layout, d_records, n, ws8, rr, wa, wb, together);
@@ -1792,7 +1794,6 @@ int32_t ltl4c_wait(ltl4c_ctx* ctx) {
         ctx->moved = false;
     } else {
         // the error word follows the work on the stream into pinned memory: one wait for both
-        if (!ctx->err_host) HIP_TRY(hipHostMalloc(&ctx->err_host, 64, hipHostMallocDefault));
         HIP_TRY(hipMemcpyAsync(ctx->err_host, ctx->err_dev, 4, hipMemcpyDeviceToHost, ctx->stream));
         HIP_TRY(hipStreamSynchronize(ctx->stream));
         err = *ctx->err_host;
