@@ -36,11 +36,10 @@ __device__ __forceinline__ uint32_t lower_bound(K key_at, uint32_t lo, uint32_t 
     return lo;
 }
 
-// the same by a whole wave over the parent array: 64 probes a round trip
-__device__ __forceinline__ uint32_t wave_lower_bound(const ParentArgs& a, const uint64_t* par, uint32_t k,
+// the same by a whole wave over entries [lo, hi) of the parent array: 64 probes a round trip
+__device__ __forceinline__ uint32_t wave_lower_bound(const ParentArgs& a, const uint64_t* par, uint32_t lo, uint32_t hi,
                                                      uint64_t target) {
     const uint32_t lane = threadIdx.x & 63u;
-    uint32_t lo = 0, hi = k;
     while (lo < hi) {
         const uint32_t step = (hi - lo + 63u) / 64u;
         const uint64_t at = (uint64_t)lo + (uint64_t)(lane + 1u) * step - 1u;    // the last of this lane's part
@@ -49,6 +48,21 @@ __device__ __forceinline__ uint32_t wave_lower_bound(const ParentArgs& a, const 
         hi = min(hi, lo + step - 1u);
     }
     return lo;
+}
+
+// pe_range by a whole wave, one round trip: the nodes that cover [l, r), at most
+// two of a level, one per lane in the order of their entries (lanes 0..31 the
+// left ones upwards, 32..63 the right ones downwards), composed by a scan.
+__device__ __forceinline__ BMap<4> wave_range(const ParentArgs& a, const uint32_t (*cm)[4], const uint64_t* par,
+                                              uint32_t p, uint32_t l, uint32_t r) {
+    const uint32_t lane = threadIdx.x & 63u, L = lane < 32u ? lane : 63u - lane;
+    const uint64_t lo = ((uint64_t)l + (1ull << L) - 1ull) >> L, hi = (uint64_t)r >> L;   // whole nodes of level L
+    const uint64_t node = lane < 32u ? lo : hi - 1u;
+    BMap<4> m = bm_identity<4>();
+    if (lo < hi && ((lane < 32u ? lo : hi) & 1u))
+        m = L == 0 ? bm_load<4>(cm[(uint32_t)par[node] & a.class_mask])
+                   : pe_unpack<4>(a.tree[a.tree_off[L] + (uint64_t)p * a.tree_cnt[L] + node]);
+    return bm_bcast<4>(bm_wave_incl_scan<4>(m), 63);
 }
 
 __device__ __forceinline__ void load_class_maps(const ParentArgs& a, uint32_t p, uint32_t (*s_cm)[4]) {
@@ -65,6 +79,7 @@ __global__ __launch_bounds__(256) void k_pe_tree(ParentArgs a, uint32_t L0, uint
     __shared__ uint4 s[256];
     __shared__ uint32_t s_cm[16][4];
     const uint32_t p = blockIdx.y;
+    if (*a.n_own == 0) return;                     // no instance to merge them into
     load_class_maps(a, p, s_cm);
     const uint32_t k = *a.n_par;
     const uint64_t* par = a.words + *a.n_own;
@@ -97,26 +112,127 @@ __global__ __launch_bounds__(256) void k_pe_tree(ParentArgs a, uint32_t L0, uint
 }
 
 // Per entry of the parent array and property (blockIdx.y): the state from q0
-// through its run up to and with it, and the map of the run from it on.
+// through its run up to and with it, and the map of the run from it on.  Both
+// are scans over the entries, forwards with the state restarted at a run's
+// first entry and backwards with the map restarted at its last: a thread takes
+// 8 consecutive entries, the block joins its threads, and where a run reaches
+// over the block's edge one wave finds its end and composes that part of it
+// from the segment tree.  Each entry so costs a few compositions however long
+// its run is.  With two tree walks per entry instead, 2M entries of one parent
+// and 16 properties took 3,055 us, 230 us so.
+constexpr int kAffixItems = 8;
+constexpr uint32_t kAffixTile = 256 * kAffixItems;
 __global__ __launch_bounds__(256) void k_pe_affix(ParentArgs a) {
     __shared__ uint32_t s_cm[16][4];
+    __shared__ uint32_t s_fwd[4][4], s_bwd[4][4], s_end[4];   // per wave: map forwards; map up to its first run end, if any
+    __shared__ uint32_t s_before, s_after[4];
     const uint32_t p = blockIdx.y;
+    const uint32_t k = *a.n_par, n_own = *a.n_own, q0 = a.plan->prop[p].q0;
+    if (n_own == 0) return;                      // no instance to merge them into
     load_class_maps(a, p, s_cm);
-    const uint32_t k = *a.n_par, q0 = a.plan->prop[p].q0;
-    const uint64_t* par = a.words + *a.n_own;
-    for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < k; e += gridDim.x * blockDim.x) {
-        const uint64_t pf = pe_prefix(a, par[e]);
-        auto prefix_at = [&](uint32_t i) { return pe_prefix(a, par[i]); };
-        // the run's ends, by doubling steps away from e
-        uint32_t lo = e, step = 1;               // entries [lo, e] are of the run
-        while (lo >= step && prefix_at(lo - step) == pf) lo -= step, step <<= 1;
-        const uint32_t rs = lower_bound(prefix_at, lo >= step ? lo - step + 1u : 0u, lo, pf);
-        uint32_t hi = e;                         // entries [e, hi] are of the run
-        step = 1;
-        while (step < k - hi && prefix_at(hi + step) == pf) hi += step, step <<= 1;
-        const uint32_t re = lower_bound(prefix_at, hi + 1u, step < k - hi ? hi + step : k, pf + 1u);
-        a.pre[(uint64_t)p * a.cap + e] = (uint8_t)bm_at<4>(pe_range<4>(a, s_cm, par, p, rs, e + 1u), q0);
-        a.suf[(uint64_t)p * a.cap + e] = pe_pack(pe_range<4>(a, s_cm, par, p, e, re));
+    const uint64_t* par = a.words + n_own;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
+    for (uint64_t base = (uint64_t)blockIdx.x * kAffixTile; base < k; base += (uint64_t)gridDim.x * kAffixTile) {
+        const uint64_t my0 = base + tid * kAffixItems;
+        const uint32_t cnt = my0 >= k ? 0u : min(k - (uint32_t)my0, (uint32_t)kAffixItems);
+        // (unconditional loads of clamped entries: all in flight together)
+        uint64_t pf[kAffixItems + 2];            // the prefix before, the run's, and the one after
+        uint32_t cls = 0;
+#pragma unroll
+        for (int j = 0; j < kAffixItems + 2; ++j) {
+            const uint64_t at = my0 + j > 0 ? my0 + j - 1u : 0u;
+            const uint64_t x = par[at < k ? at : k - 1u];
+            pf[j] = pe_prefix(a, x);
+            if (j > 0 && j <= kAffixItems) cls |= ((uint32_t)x & a.class_mask) << (4 * (j - 1));
+        }
+        uint32_t heads = 0, ends = 0;
+#pragma unroll
+        for (int j = 0; j < kAffixItems; ++j) {
+            heads |= (uint32_t)(my0 + j == 0 || pf[j] != pf[j + 1]) << j;
+            ends |= (uint32_t)(my0 + j + 1 == k || pf[j + 1] != pf[j + 2]) << j;
+        }
+        auto map_of = [&](int j) { return bm_load<4>(s_cm[(cls >> (4 * j)) & 15u]); };
+        BMap<4> f = bm_identity<4>(), b = bm_identity<4>();
+        uint32_t ended = 0;
+#pragma unroll
+        for (int j = 0; j < kAffixItems; ++j) {
+            if ((uint32_t)j >= cnt) continue;
+            const BMap<4> c = map_of(j);
+            f = bm_compose<4>(c, ((heads >> j) & 1u) ? bm_const<4>(q0) : f);
+            if (!ended) b = bm_compose<4>(c, b);
+            ended |= (ends >> j) & 1u;
+        }
+        f = bm_wave_incl_scan<4>(f);
+        const BMap<4> fx = bm_wave_shr1<4>(f);   // of the lanes before
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) { // of this lane and those after it, up to a run end
+            const BMap<4> later = bm_shfl_down<4>(b, off);
+            const uint32_t e = __shfl_down(ended, off, 64);
+            if (lane + off < 64u && !ended) {
+                b = bm_compose<4>(later, b);
+                ended = e;
+            }
+        }
+        BMap<4> bx = bm_shfl_down<4>(b, 1);      // of the lanes after alone
+        uint32_t ex = __shfl_down(ended, 1, 64);
+        if (lane == 63u) {
+            bx = bm_identity<4>();
+            ex = 0;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (lane == 63u) s_fwd[w][i] = f.d[i];
+            if (lane == 0u) s_bwd[w][i] = b.d[i];
+        }
+        if (lane == 0u) s_end[w] = ended;
+        if (w == 0) {                            // the run that reaches into the tile
+            const uint64_t first = __shfl(pf[1], 0, 64);
+            uint32_t s = q0;
+            if (!(__shfl(heads, 0, 64) & 1u)) {
+                const uint32_t rs = wave_lower_bound(a, par, 0u, (uint32_t)base, first << a.ibits);
+                s = bm_at<4>(wave_range(a, s_cm, par, p, rs, (uint32_t)base), q0);
+            }
+            if (lane == 0u) s_before = s;
+        } else if (w == 3) {                     // the run that reaches out of it
+            BMap<4> m = bm_identity<4>();
+            const uint32_t next = min((uint32_t)base + kAffixTile, k);
+            const uint64_t last = pe_prefix(a, par[next - 1u]);
+            if (next < k && pe_prefix(a, par[next]) == last) {
+                const uint32_t re = wave_lower_bound(a, par, next, k, (last + 1u) << a.ibits);
+                m = wave_range(a, s_cm, par, p, next, re);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (lane == 0u) s_after[i] = m.d[i];
+        }
+        __syncthreads();
+        uint32_t s = s_before;
+        for (uint32_t i = 0; i < w; ++i) s = bm_at<4>(bm_load<4>(s_fwd[i]), s);
+        s = bm_at<4>(fx, s);
+        for (uint32_t i = w + 1; i < 4 && !ex; ++i) {
+            bx = bm_compose<4>(bm_load<4>(s_bwd[i]), bx);
+            ex = s_end[i];
+        }
+        if (!ex) bx = bm_compose<4>(bm_load<4>(s_after), bx);
+        uint32_t out[2] = {0, 0};
+#pragma unroll
+        for (int j = 0; j < kAffixItems; ++j) {
+            s = bm_at<4>(map_of(j), ((heads >> j) & 1u) ? q0 : s);
+            out[j >> 2] |= s << (8 * (j & 3));
+        }
+        uint8_t* pre = a.pre + (uint64_t)p * a.cap + my0;
+        if (cnt == kAffixItems) __builtin_memcpy(pre, out, 8);
+        else
+            for (uint32_t j = 0; j < cnt; ++j) pre[j] = (uint8_t)(out[j >> 2] >> (8 * (j & 3)));
+        uint2* suf = a.suf + (uint64_t)p * a.cap + my0;
+#pragma unroll
+        for (int j = kAffixItems - 1; j >= 0; --j) {
+            if ((uint32_t)j >= cnt) continue;
+            const BMap<4> c = map_of(j);
+            bx = ((ends >> j) & 1u) ? c : bm_compose<4>(bx, c);
+            suf[j] = pe_pack(bx);
+        }
+        __syncthreads();                         // every thread has read the block's totals
     }
 }
 
@@ -206,7 +322,7 @@ __global__ __launch_bounds__(kPeThreads) void k_pe_bounds(ParentArgs a) {
     const uint32_t tid = threadIdx.x, wave = tid >> 6;
     if (wave < 2) {
         const uint64_t at = wave == 0 ? base : min<uint64_t>(base + kPeTile, n_own) - 1u;
-        const uint32_t b = wave_lower_bound(a, par, k, (pe_prefix(a, a.words[at]) + wave) << a.ibits);
+        const uint32_t b = wave_lower_bound(a, par, 0u, k, (pe_prefix(a, a.words[at]) + wave) << a.ibits);
         if ((tid & 63u) == 0) s_part[wave] = b;
     }
     __syncthreads();
@@ -233,7 +349,7 @@ hipError_t launch_parent_tree(const ParentArgs& a, uint32_t level0, uint32_t nle
 }
 
 hipError_t launch_parent_affix(const ParentArgs& a, uint64_t max_entries, hipStream_t s) {
-    const uint64_t want = (max_entries + 255) / 256;
+    const uint64_t want = (max_entries + kAffixTile - 1) / kAffixTile;
     hipLaunchKernelGGL(k_pe_affix, dim3((uint32_t)(want < 1024 ? (want ? want : 1) : 1024), a.n_props), dim3(256), 0, s, a);
     return hipGetLastError();
 }
