@@ -180,10 +180,12 @@ constexpr int kMsThreads = 256;
 constexpr int kMsSpineThreads = 1024;  // the spine block; a spine chunk holds at least this many tiles
 constexpr int kMsTileMin = kMsThreads * 16;   // workspace arrays are sized for the smaller tile
 // Up to this many tiles every block of the down sweep composes what comes
-// before it by itself instead of waiting for a spine block, a launch less: 1M
-// words, one property, down sweep 9.0 us and spine 5.0 -> 9.9 us; 10M words 19.3
-// and 11.7 -> 26.6 us.  The records read grow with the square of the tiles, so
-// longer traces keep the spine.
+// before it by itself instead of waiting for a spine block, a launch less; the
+// records read grow with the square of the tiles.  All launches of the map scan,
+// own prefixes and spine: one property 1M words 18.9 and 23.2 us, 10M (2,442
+// tiles) 47.8 and 50.4, 12M (2,930) 55.2 and 55.3, 14M 62.5 and 59.6, 32M 188 and
+// 127; four 16-state monitors (80-byte records) 10M 98.5 and 113, 12M 116 and 125,
+// 14M 138 and 133.  The two cross near 3,000 tiles; the line lies below that.
 constexpr uint32_t kOwnTiles = 2560;
 constexpr int kMsRec = 4 + 16;
 constexpr uint32_t kRootCopies = 16;  // copies of a one-level tree's root bins (tiles add to the same words)

@@ -18,7 +18,7 @@
 //     so that the two gaps every instance has cost one look-up each;
 //   * a segment tree over P of composed class maps (level L node q composes
 //     the entries [q 2^L, (q+1) 2^L)), built eight levels per launch in LDS,
-//     for the gaps inside an instance.
+//     for the gaps inside an instance and for runs that reach over a block.
 #include "parent.h"
 
 namespace ltl4c {
