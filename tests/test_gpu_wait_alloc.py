@@ -39,3 +39,53 @@ def test_first_wait_allocates_nothing():
     calls = re.findall(r"\b(hip[A-Z]\w*)\s*\(", log)
     assert "hipStreamSynchronize" in calls           # the log is on
     assert not [c for c in calls if re.search("Malloc|HostAlloc|HostRegister", c)], sorted(set(calls))
+
+
+def test_error_words_of_many_contexts():
+    """More contexts at a time than the page of host words has room for, some
+    closed and made again, two threads at it: every context reports its own
+    errors and no other's."""
+    import threading
+
+    import torch
+    from paper_1411_2239_amd import lib, workloads as W
+    good = torch.zeros((64, 4), dtype=torch.int32, device="cuda:0")
+    bad = good.clone()
+    bad[5, 2] = 1 << 12                              # a key wider than declared
+    good, bad = good.view(torch.uint8).reshape(-1), bad.view(torch.uint8).reshape(-1)
+
+    def make():
+        ctx = lib.Context(0)
+        ctx.set_layout(W.prop_layout(3, 1, [10]))
+        ids = [ctx.add_spec(W.PropertySpec("G a", [("A", ">=", "1/2")], "p"))]
+        return ctx, ids, ctx.alloc_result(1), ctx.workspace(64, ids)
+
+    failures = []
+
+    def work(k):
+        try:
+            all_ctx = [make() for _ in range(40)]
+            for ctx, *_ in all_ctx[::3]:
+                ctx.close()
+            all_ctx = [make() if i % 3 == 0 else c for i, c in enumerate(all_ctx)]
+            for i, (ctx, ids, r, ws) in enumerate(all_ctx):
+                ctx.eval_into(bad if (i + k) % 2 else good, 64, ids, r, ws)
+            for i, (ctx, *_) in enumerate(all_ctx):
+                try:
+                    ctx.wait()
+                    got = lib.OK
+                except lib.LTL4CError as e:
+                    got = e.status
+                if got != (lib.ERANGE if (i + k) % 2 else lib.OK):
+                    failures.append((k, i, got))
+                ctx.close()
+        except Exception as e:                       # (a thread's failure would be lost)
+            failures.append((k, repr(e)))
+
+    print("[case] 80 contexts in two threads", flush=True)
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures, failures[:5]
