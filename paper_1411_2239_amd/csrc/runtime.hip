@@ -94,6 +94,8 @@ hipError_t scratch_address(int device, uint8_t** out) {
 // their own.  A context gives its words back once nothing that writes them is in
 // flight.
 constexpr uint32_t kHostWords = 16, kHostSlots = 64;
+// (kernels write the distinct counts straight into them, of whichever device)
+constexpr unsigned kHostFlags = hipHostMallocPortable | hipHostMallocCoherent;
 std::mutex g_host_mu;
 uint32_t* g_host_page = nullptr;
 uint64_t g_host_used = 0;
@@ -101,13 +103,13 @@ uint64_t g_host_used = 0;
 hipError_t take_host_words(uint32_t** out) {
     std::lock_guard<std::mutex> lk(g_host_mu);
     if (!g_host_page) {
-        const hipError_t e = hipHostMalloc(&g_host_page, 4 * kHostWords * kHostSlots, hipHostMallocPortable);
+        const hipError_t e = hipHostMalloc(&g_host_page, 4 * kHostWords * kHostSlots, kHostFlags);
         if (e != hipSuccess) {
             g_host_page = nullptr;
             return e;
         }
     }
-    if (g_host_used == ~0ull) return hipHostMalloc(out, 4 * kHostWords, hipHostMallocPortable);
+    if (g_host_used == ~0ull) return hipHostMalloc(out, 4 * kHostWords, kHostFlags);
     const uint32_t i = (uint32_t)__builtin_ctzll(~g_host_used);
     g_host_used |= 1ull << i;
     *out = g_host_page + kHostWords * i;
